@@ -6,10 +6,11 @@
 // item is one tile (a, b) processed by one wave; each lane keeps R "resident"
 // rows of block a in registers.
 //  - Symmetric tiles (a < b): the 64-position sub-blocks of b travel around the
-//    wave (a DPP rotation by one lane per step), so every unordered pair
-//    (i, j) is met exactly once; w_ij is computed once and its force is added
-//    to the resident row (+) and to the travelling column (-).  After 64 steps
-//    each travelling position is back in its own lane with its column sum.
+//    wave (every lane reads the next column from LDS, and a column's force
+//    moves one lane on per step), so every unordered pair (i, j) is met exactly
+//    once; w_ij is computed once and its force is added to the resident row (+)
+//    and to the travelling column (-).  After 64 steps each column's sum is
+//    back in the column's own lane.
 //  - Direct tiles (every tile of the direct variant): columns of b are read as
 //    wave-uniform values and each ordered pair is computed by the row's lane;
 //    the i == j term is masked by index.  Diagonal tiles of the symmetric
@@ -61,55 +62,111 @@ __device__ __forceinline__ float student_w(float dx, float dy) {
   return __builtin_amdgcn_rcpf(__builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f)));
 }
 
+// Two values the compiler keeps in an aligned pair of registers, the first in
+// an even one and the second in the odd one after it.  A three-operand FP32
+// instruction whose operands all sit in registers of one parity takes 4.6
+// cycles per wave, any other 2.4 (measured with 8 waves per SIMD), and left to
+// itself the compiler lets a third of the loop's FMAs fall on one parity.
+typedef float reg_pair __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ void keep_paired(reg_pair& v) { asm("" : "+v"(v)); }
+
+// Rows whose reciprocals are issued back to back (see sym_step).
+template <int R>
+constexpr int recip_group() {
+  return R == 15 ? 3 : R == 12 ? 6 : R == 14 ? 7 : R >= 8 ? 4 : R >= 2 ? 2 : 1;
+}
+
 // One step of a symmetric tile: the R resident rows of this lane against the
-// travelling column now in it.  The step's Z terms go on the chain zs;
-// OPENS starts that chain at the first weight rather than adding it to +0
-// (an add the compiler must keep, as -0 + 0 = +0; no weight is -0).
+// column c now in it.  The step's Z terms go on the chain zs; OPENS starts
+// that chain at the first weight rather than adding it to +0 (an add the
+// compiler must keep, as -0 + 0 = +0; no weight is -0).  res holds the rows'
+// sums and s the column's, both as (y, x).
 // FORCES = false keeps only the Z terms (the same weights, added in the same
 // order, so Z is bitwise the one the force pass gives).
-template <int R, bool MASKED, bool OPENS, bool FORCES = true>
-__device__ __forceinline__ void sym_step(const float (&yix)[R], const float (&yiy)[R], float (&rix)[R],
-                                         float (&riy)[R], float& tx, float& ty, float& fx, float& fy, float& m,
-                                         float& zs) {
-  float sx = 0.f, sy = 0.f;
+//
+// What a step costs is issue: an FP32 add, mul or FMA takes 2.4 cycles per
+// wave as long as two waves' such instructions can be issued side by side, a
+// reciprocal 8.3 and whatever else its place among them breaks up.  So the
+// reciprocals of recip_group rows go out together, at a raised wave priority
+// so that no other wave's instructions fall between them (10 FMAs and a
+// reciprocal: 47 cycles alternating, 37 in groups of four, 31 with the
+// priority), and the operands are kept in registers of both parities.
+// Measured at 300,000 nodes, 15 rows: 11.27 -> 9.43 ms a launch, 39.4 -> 33.0
+// cycles per pair of a wave, of a least 10 * 2.4 + 8.3 = 32.3.
+template <int R, bool MASKED, bool OPENS, bool FORCES>
+__device__ __forceinline__ void sym_step(const float2 (&y)[R], reg_pair (&res)[R], reg_pair (&tw)[recip_group<R>()],
+                                         float2 c, float m, float& zs, reg_pair& s) {
+  constexpr int G = recip_group<R>();
+  s = reg_pair{0.f, 0.f};
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const float dx = yix[r] - tx, dy = yiy[r] - ty;
-    float w = student_w(dx, dy);
-    if (MASKED) w *= m;
-    zs = (OPENS && r == 0) ? w : zs + w;
-    if (FORCES) {
-      const float w2 = w * w;
-      rix[r] = __builtin_fmaf(w2, dx, rix[r]);
-      riy[r] = __builtin_fmaf(w2, dy, riy[r]);
-      sx = __builtin_fmaf(w2, dx, sx);
-      sy = __builtin_fmaf(w2, dy, sy);
+  for (int r0 = 0; r0 < R; r0 += G) {
+    reg_pair d[G];  // (dx, dy)
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (r0 + g >= R) continue;
+      d[g] = reg_pair{y[r0 + g].x - c.x, y[r0 + g].y - c.y};
+      keep_paired(d[g]);
+      tw[g].y = __builtin_fmaf(d[g].y, d[g].y, 1.0f);  // tw: (w^2, w)
+      keep_paired(tw[g]);
+      tw[g].y = __builtin_fmaf(d[g].x, d[g].x, tw[g].y);
+    }
+    // w = 1 / (1 + dx^2 + dy^2) with the hardware reciprocal (<= 1 ulp)
+    if (G > 1) __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (r0 + g < R) tw[g].y = __builtin_amdgcn_rcpf(tw[g].y);
+    if (G > 1) __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int r = r0 + g;
+      if (r >= R) continue;
+      if (MASKED) tw[g].y *= m;
+      zs = (OPENS && r == 0) ? tw[g].y : zs + tw[g].y;
+      if (FORCES) {
+        tw[g].x = tw[g].y * tw[g].y;
+        res[r] = reg_pair{__builtin_fmaf(tw[g].x, d[g].y, res[r].x), __builtin_fmaf(tw[g].x, d[g].x, res[r].y)};
+        keep_paired(res[r]);
+        s = reg_pair{__builtin_fmaf(tw[g].x, d[g].y, s.x), __builtin_fmaf(tw[g].x, d[g].x, s.y)};
+        keep_paired(s);
+      }
     }
   }
-  // the column's travelling force trails it by one lane: carried across
-  // and reduced in one instruction
-  if (FORCES) {
-    fx = rotate_lanes_once(fx) - sx;
-    fy = rotate_lanes_once(fy) - sy;
-  }
-  tx = rotate_lanes(tx);
-  ty = rotate_lanes(ty);
-  if (MASKED) m = rotate_lanes(m);
 }
 
 // A 64-step pass of a symmetric tile (a < b; block a is always full,
-// a < nb - 1).  Accumulation is two-level to keep FP32 chains short: the
-// travelling sum of one step (R terms) is formed apart and then added, the
-// resident sums are folded into a second FP32 sum after every pass, and Z is
-// summed in FP32 over two steps (2R terms) before its FP64 sum.
-template <int R, bool SPLIT, bool MASKED, bool FORCES = true>
-__device__ __forceinline__ void sym_pass(const float (&yix)[R], const float (&yiy)[R], float (&rix)[R],
-                                         float (&riy)[R], float& tx, float& ty, float& fx, float& fy, float& m,
-                                         double& z64, float& z32) {
-  for (int s = 0; s < kWave; s += 2) {
-    float zs;
-    sym_step<R, MASKED, true, FORCES>(yix, yiy, rix, riy, tx, ty, fx, fy, m, zs);
-    sym_step<R, MASKED, false, FORCES>(yix, yiy, rix, riy, tx, ty, fx, fy, m, zs);
+// a < nb - 1): in step t lane l meets column (l - t) mod 64, read from cols,
+// which holds the 64 columns twice so that a step is a fixed offset.  A
+// column's force trails it by one lane: it is carried across and reduced in
+// one instruction, by the DPP operand of the subtraction.  Accumulation is
+// two-level to keep FP32 chains short: the travelling sum of one step (R
+// terms) is formed apart and then added, the resident sums are folded into a
+// second FP32 sum after every pass, and Z is summed in FP32 over two steps (2R
+// terms) before its FP64 sum.  MASKED: columns from `valid` on count for nothing.
+template <int R, bool SPLIT, bool MASKED, bool FORCES>
+__device__ __forceinline__ void sym_pass(const float2 (&y)[R], reg_pair (&res)[R], reg_pair (&tw)[recip_group<R>()],
+                                         const float2* cols, int lane, int valid, float& fx, float& fy, double& z64,
+                                         float& z32) {
+  // One row per lane is the tile of graphs too small to fill the chip, where a
+  // wave's own latency counts: its columns rotate through the lanes instead.
+  constexpr bool kRotate = R == 1;
+  const float2* mine = cols + kWave + lane;
+  float2 c = mine[0];
+  for (int t = 0; t < kWave; t += 2) {
+    float zs = 0.f;
+    reg_pair s;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (!kRotate) c = mine[-(t + u)];
+      const float m = !MASKED || ((lane - t - u) & (kWave - 1)) < valid ? 1.f : 0.f;
+      if (u == 0) sym_step<R, MASKED, true, FORCES>(y, res, tw, c, m, zs, s);
+      else sym_step<R, MASKED, false, FORCES>(y, res, tw, c, m, zs, s);
+      if (FORCES) {
+        fx = rotate_lanes_once(fx) - s.y;
+        fy = rotate_lanes_once(fy) - s.x;
+      }
+      if (kRotate) c = make_float2(rotate_lanes(c.x), rotate_lanes(c.y));
+    }
     if (SPLIT) z64 += (double)zs; else z32 += zs;
   }
   // after the last step the forces are one lane short of their columns
@@ -119,47 +176,62 @@ __device__ __forceinline__ void sym_pass(const float (&yix)[R], const float (&yi
   }
 }
 
+// Orders a wave's own accesses to LDS by other lanes (the hardware keeps them
+// in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// cols: this wave's 2 * kWave columns of LDS.  Reading the travelling
+// positions from LDS takes two DPP moves per step (4.3 cycles each, and
+// nothing else is issued beside them) off the vector pipe.
 template <int R, bool SPLIT, bool FORCES = true>
 __device__ __forceinline__ void tile_symmetric(const float2* __restrict__ Y, int32_t n, int32_t nb, int32_t a, int32_t b,
                                float2* __restrict__ part, double* __restrict__ zpart, float* __restrict__ zpart32,
-                               int64_t item, int lane) {
+                               int64_t item, int lane, float2* cols) {
   constexpr int T = kWave * R;
+  constexpr int G = recip_group<R>();
   const int32_t valid_b = min(T, n - b * T);
-  float yix[R], yiy[R], rix[R], riy[R], hix[R], hiy[R];
+  float2 y[R];
+  reg_pair res[R], sum[R], tw[G];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const float2 v = Y[(int64_t)a * T + r * kWave + lane];
-    yix[r] = v.x;
-    yiy[r] = v.y;
-    rix[r] = riy[r] = hix[r] = hiy[r] = 0.f;
+    y[r] = Y[(int64_t)a * T + r * kWave + lane];
+    res[r] = sum[r] = reg_pair{0.f, 0.f};
   }
+#pragma unroll
+  for (int g = 0; g < G; ++g) tw[g] = reg_pair{0.f, 0.f};
   double z64 = 0.0;
   float z32 = 0.f;
+#pragma unroll 1
   for (int q = 0; q < R; ++q) {
     if (q * kWave >= valid_b) break;  // wave-uniform
     const int jl = q * kWave + lane;
     const bool vj = jl < valid_b;
     const float2 v = vj ? Y[(int64_t)b * T + jl] : make_float2(0.f, 0.f);
-    float tx = v.x, ty = v.y, fx = 0.f, fy = 0.f;
-    // partially valid sub-block (last block only): the mask travels with its position
-    float m = vj ? 1.f : 0.f;
-    if (q * kWave + kWave <= valid_b)
-      sym_pass<R, SPLIT, false, FORCES>(yix, yiy, rix, riy, tx, ty, fx, fy, m, z64, z32);
-    else
-      sym_pass<R, SPLIT, true, FORCES>(yix, yiy, rix, riy, tx, ty, fx, fy, m, z64, z32);
+    wave_lds_fence();
+    cols[lane] = v;
+    cols[lane + kWave] = v;
+    wave_lds_fence();
+    float fx = 0.f, fy = 0.f;
+    // a partially valid sub-block (last block only) is masked
+    const int valid = valid_b - q * kWave;
+    if (valid >= kWave) sym_pass<R, SPLIT, false, FORCES>(y, res, tw, cols, lane, valid, fx, fy, z64, z32);
+    else sym_pass<R, SPLIT, true, FORCES>(y, res, tw, cols, lane, valid, fx, fy, z64, z32);
     if (FORCES) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        hix[r] += rix[r];
-        hiy[r] += riy[r];
-        rix[r] = riy[r] = 0.f;
+        sum[r] = reg_pair{sum[r].x + res[r].x, sum[r].y + res[r].y};
+        res[r] = reg_pair{0.f, 0.f};
       }
       if (vj) part[((int64_t)b * nb + a) * T + jl] = make_float2(fx, fy);
     }
   }
   if (FORCES) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) part[((int64_t)a * nb + b) * T + r * kWave + lane] = make_float2(hix[r], hiy[r]);
+    for (int r = 0; r < R; ++r)
+      part[((int64_t)a * nb + b) * T + r * kWave + lane] = make_float2(sum[r].y, sum[r].x);
   }
   // every unordered pair stands for the two ordered pairs of Z
   if (SPLIT) {
@@ -322,16 +394,14 @@ __device__ __forceinline__ void tile_diag_light(const float2* __restrict__ Y, in
   }
 }
 
-// Waves per SIMD the repulsion kernels must allow.  With few rows per lane a
-// step holds too few independent pairs to hide the dependent-issue latency
-// at the 4 waves per SIMD the compiler's default register budget gives
-// (measured with R = 8: 37 % more cycles waiting on dependencies than R = 16
-// for 4 % more VALU instructions).  Asking for 6 keeps R = 8 at 69 VGPRs
-// (7 waves per SIMD) and 5 keeps R = 12 at 93 (5 waves), both without
-// spills; R >= 14 would spill below 4 waves and keeps the default.
+// Waves per SIMD the repulsion kernels must allow: with fewer, two waves'
+// FP32 instructions are side by side less often (an FMA issues every 3.1
+// cycles with 4 waves per SIMD, every 2.4 with 8).  R <= 4 fits 8 waves
+// without spills; at R = 8 and from R = 14 on a few of the sums that the inner
+// loop does not touch are spilled.
 template <int R>
 constexpr int repulse_min_waves() {
-  return R <= 8 ? 6 : R <= 12 ? 5 : 1;
+  return R <= 4 ? 8 : R <= 8 ? 6 : R <= 16 ? 4 : 1;
 }
 
 template <int R, bool SPLIT, bool SYM>
@@ -345,8 +415,10 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_repulse(cons
   const int lane = threadIdx.x & (kWave - 1);
   const int2 ab = items[item];
   const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
+  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  float2* cols = s_cols[threadIdx.x >> 6];
   if (SYM) {
-    if (a != b) tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane);
+    if (a != b) tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, cols);
     else tile_diag_light<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, lane);
   } else {
     tile_direct<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane);
@@ -366,8 +438,10 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
   const int lane = threadIdx.x & (kWave - 1);
   const int2 ab = items[item];
   const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
+  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  float2* cols = s_cols[threadIdx.x >> 6];
   if (SYM) {
-    if (a != b) tile_symmetric<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane);
+    if (a != b) tile_symmetric<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane, cols);
     else tile_diag_light<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, lane);
   } else {
     tile_direct<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane);
@@ -684,7 +758,9 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_repuls
   const int lane = threadIdx.x & (kWave - 1);
   const int32_t a = __builtin_amdgcn_readfirstlane(it.y), b = __builtin_amdgcn_readfirstlane(it.z);
   const int64_t li = __builtin_amdgcn_readfirstlane(it.w);
-  if (a != b) tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane);
+  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  float2* cols = s_cols[threadIdx.x >> 6];
+  if (a != b) tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane, cols);
   else tile_diag_light<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, li, lane);
 }
 
