@@ -292,12 +292,12 @@ tsgne_status ensure_workspace(tsgne_graph* g, const tsgne_params* p) {
   free_workspace(ws);
   ws.plan = want;
   const RepulsionPlan& pl = ws.plan;
-  // Symmetric plans dispatch the diagonal tiles (one resident row per lane
-  // per pass, the slower kind) first, then the off-diagonal tiles row by row,
-  // and last the tiles against the last block (a, nb - 1), which is partly
-  // filled when T does not divide n: the launch's tail is made of its
-  // shortest tiles.  A tile's position in this list is also its Z partial's
-  // slot, i.e. Z's summation order.
+  // Symmetric plans list the diagonal tiles first (they are dispatched last: a
+  // workgroup each, they are the shortest), then the off-diagonal tiles row by
+  // row, and last the tiles against the last block (a, nb - 1), which is partly
+  // filled when T does not divide n: the launch's tail is made of its shortest
+  // tiles.  A tile's position in this list is also its Z partial's slot, i.e.
+  // Z's summation order.
   std::vector<int2> items;
   items.reserve((size_t)pl.items);
   if (pl.variant == TSGNE_REPULSION_DIRECT) {

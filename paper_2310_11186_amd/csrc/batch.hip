@@ -76,8 +76,9 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
       for (int32_t r : h) heavy.push_back(make_int2(k, r));
     }
   }
-  // diagonal tiles (one row per lane per pass, the slower kind) go first,
-  // the tiles against each graph's partly filled last block last
+  // diagonal tiles (a workgroup each) first in the list, the tiles against each
+  // graph's partly filled last block last
+  bp_.n_diag = (int64_t)diag_items.size();
   diag_items.insert(diag_items.end(), items.begin(), items.end());
   diag_items.insert(diag_items.end(), last_items.begin(), last_items.end());
   bp_.n_items = (int64_t)diag_items.size();

@@ -37,7 +37,8 @@ struct RepulsionPlan {
   int32_t T = 0;        // block length = 64 * R
   int32_t nb = 0;       // number of blocks, the last one possibly partial
   int32_t variant = 0;  // TSGNE_REPULSION_DIRECT or _SYMMETRIC
-  int64_t items = 0;    // work items (one wave each)
+  int64_t items = 0;    // work items (tiles)
+  int64_t diag = 0;     // diagonal tiles of a symmetric plan: the first items of its list
 };
 
 struct Workspace {
@@ -90,11 +91,12 @@ struct BatchDesc {
 // Launch tables of a batch (all device pointers).
 struct BatchPlan {
   BatchDesc* descs = nullptr;
-  int4* items = nullptr;          // (graph, a, b, item index within the graph)
+  int4* items = nullptr;          // (graph, a, b, item index within the graph), diagonal tiles first
   int2* light_chunks = nullptr;   // (graph, first row) per 32-row block
   int2* heavy = nullptr;          // (graph, row) per heavy row
   int2* row_blocks = nullptr;     // (graph, first row) per 256-row block
   int64_t n_items = 0;
+  int64_t n_diag = 0;
   int32_t n_light_chunks = 0;
   int32_t n_heavy = 0;
   int32_t n_row_blocks = 0;

@@ -130,21 +130,23 @@ __global__ __launch_bounds__(kReduceBlock) void k_shard_zero(int32_t n, double2*
 
 int32_t owner_host(int32_t a, int32_t nb, int32_t n_shards) { return std::min(a, nb - 1 - a) % n_shards; }
 
-// Tiles of the shard for tile rows R, a ascending then b ascending.
+// Tiles of the shard for tile rows R: its diagonal tiles, then the others, a
+// ascending then b ascending.
 std::vector<int2> shard_tiles(int32_t n, int32_t R, int32_t shard, int32_t n_shards, int64_t* pairs) {
   const int64_t T = (int64_t)kWave * R;
   const int32_t nb = (int32_t)((n + T - 1) / T);
-  std::vector<int2> items;
+  std::vector<int2> items, rest;
   int64_t pr = 0;
   for (int32_t a = 0; a < nb; ++a) {
     if (owner_host(a, nb, n_shards) != shard) continue;
     const int64_t va = std::min<int64_t>(T, (int64_t)n - a * T);
     for (int32_t b = a; b < nb; ++b) {
-      items.push_back(make_int2(a, b));
+      (a == b ? items : rest).push_back(make_int2(a, b));
       const int64_t vb = std::min<int64_t>(T, (int64_t)n - b * T);
       pr += a == b ? va * (va - 1) : 2 * va * vb;
     }
   }
+  items.insert(items.end(), rest.begin(), rest.end());
   *pairs = pr;
   return items;
 }
@@ -241,6 +243,7 @@ tsgne_status tsgne_shard_create(int32_t n, int32_t shard, int32_t n_shards, int3
     }
   }
   sh->n_owned = (int32_t)owned.size();
+  ws.plan.diag = (int64_t)owned.size();  // one diagonal tile per row block
   hipError_t e = hipSuccess;
   if (!items.empty()) {
     e = dalloc(&ws.items, items.size());

@@ -14,7 +14,7 @@
 //  - Direct tiles (every tile of the direct variant): columns of b are read as
 //    wave-uniform values and each ordered pair is computed by the row's lane;
 //    the i == j term is masked by index.  Diagonal tiles of the symmetric
-//    variant use the same scheme one resident row at a time.
+//    variant use the same scheme one resident row at a time, by a workgroup each.
 // Each tile writes its row sums to part[a][b] and (symmetric) its column sums
 // to part[b][a], so part[k][*] holds every contribution to block k exactly
 // once and the update kernel adds them in a fixed order: results do not
@@ -327,71 +327,105 @@ __device__ __forceinline__ void tile_direct(const float2* __restrict__ Y, int32_
   }
 }
 
-// Diagonal tile (a, a) inside the symmetric kernel: one resident row per lane
-// per pass (few registers, so the symmetric path keeps its occupancy), every
-// ordered pair i != j, four interleaved partial sums per coordinate.
+// The columns cols[0 .. count) against this lane's row, every ordered pair, in
+// four interleaved partial sums per coordinate; SELF leaves out column `lane`.
+// Adds the row's force to h (y, x) and returns the sum of the weights.
+template <bool SELF, bool FORCES>
+__device__ __forceinline__ float diag_chunk(float2 yi, const float2* cols, int count, int lane, reg_pair& h) {
+  reg_pair acc[4], tw[4];
+  float az[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) acc[k] = tw[k] = reg_pair{0.f, 0.f};
+  int j = 0;
+#pragma unroll 2
+  for (; j + 4 <= count; j += 4) {
+    reg_pair d[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float2 c = cols[j + k];
+      d[k] = reg_pair{yi.x - c.x, yi.y - c.y};
+      keep_paired(d[k]);
+      tw[k].y = __builtin_fmaf(d[k].y, d[k].y, 1.0f);
+      keep_paired(tw[k]);
+      tw[k].y = __builtin_fmaf(d[k].x, d[k].x, tw[k].y);
+    }
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tw[k].y = __builtin_amdgcn_rcpf(tw[k].y);
+    __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (SELF) tw[k].y = j + k == lane ? 0.f : tw[k].y;
+      az[k] += tw[k].y;
+      if (FORCES) {
+        tw[k].x = tw[k].y * tw[k].y;
+        acc[k] = reg_pair{__builtin_fmaf(tw[k].x, d[k].y, acc[k].x), __builtin_fmaf(tw[k].x, d[k].x, acc[k].y)};
+        keep_paired(acc[k]);
+      }
+    }
+  }
+  for (; j < count; ++j) {
+    const float2 c = cols[j];
+    const float dx = yi.x - c.x, dy = yi.y - c.y;
+    float w = student_w(dx, dy);
+    if (SELF) w = j == lane ? 0.f : w;
+    az[0] += w;
+    if (FORCES) {
+      const float w2 = w * w;
+      acc[0] = reg_pair{__builtin_fmaf(w2, dy, acc[0].x), __builtin_fmaf(w2, dx, acc[0].y)};
+    }
+  }
+  if (FORCES) {
+    h.x += (acc[0].x + acc[1].x) + (acc[2].x + acc[3].x);
+    h.y += (acc[0].y + acc[1].y) + (acc[2].y + acc[3].y);
+  }
+  return (az[0] + az[1]) + (az[2] + az[3]);
+}
+
+// Diagonal tile (a, a) inside the symmetric kernel, by a whole workgroup: each
+// wave takes every kWavesPerBlock-th group of 64 rows, one row per lane,
+// against all columns of the block (every ordered pair i != j), read from LDS
+// as one address for all lanes.  On one wave, with the columns in scalar
+// registers, such a tile took 1.5 times an off-diagonal one's time and was all
+// that graphs of some ten thousand nodes waited for (8 rows per lane at 31,013
+// nodes: 0.176 -> 0.146 ms a launch; 12 rows: 0.39 -> 0.23).  s_z: one double
+// per wave.
 template <int R, bool SPLIT, bool FORCES = true>
-__device__ __forceinline__ void tile_diag_light(const float2* __restrict__ Y, int32_t n, int32_t nb, int32_t a,
-                                float2* __restrict__ part, double* __restrict__ zpart, float* __restrict__ zpart32,
-                                int64_t item, int lane) {
+__device__ __forceinline__ void tile_diag(const float2* __restrict__ Y, int32_t n, int32_t nb, int32_t a,
+                                          float2* __restrict__ part, double* __restrict__ zpart,
+                                          float* __restrict__ zpart32, int64_t item, int wave, int lane, float2* cols,
+                                          double* s_z) {
   constexpr int T = kWave * R;
   const int32_t valid = min(T, n - a * T);
   const float2* __restrict__ Ya = Y + (int64_t)a * T;
   double z64 = 0.0;
   float z32 = 0.f;
-  for (int r = 0; r < R; ++r) {
+  for (int r = wave; r * kWave < valid; r += kWavesPerBlock) {
     const int il = r * kWave + lane;
-    if (r * kWave >= valid) break;  // wave-uniform
     const bool vi = il < valid;
     const float2 yi = vi ? Ya[il] : make_float2(0.f, 0.f);
-    float hx = 0.f, hy = 0.f;
-    for (int j0 = 0; j0 < valid; j0 += kWave) {
-      const int j1 = min(j0 + kWave, valid);
-      float ax[4] = {0.f, 0.f, 0.f, 0.f}, ay[4] = {0.f, 0.f, 0.f, 0.f}, az[4] = {0.f, 0.f, 0.f, 0.f};
-      int jl = j0;
-      for (; jl + 4 <= j1; jl += 4) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float2 v = Ya[jl + k];
-          const float dx = yi.x - v.x, dy = yi.y - v.y;
-          float w = student_w(dx, dy);
-          w = (vi && jl + k != il) ? w : 0.f;
-          az[k] += w;
-          if (FORCES) {
-            const float w2 = w * w;
-            ax[k] = __builtin_fmaf(w2, dx, ax[k]);
-            ay[k] = __builtin_fmaf(w2, dy, ay[k]);
-          }
-        }
-      }
-      for (; jl < j1; ++jl) {
-        const float2 v = Ya[jl];
-        const float dx = yi.x - v.x, dy = yi.y - v.y;
-        float w = student_w(dx, dy);
-        w = (vi && jl != il) ? w : 0.f;
-        az[0] += w;
-        if (FORCES) {
-          const float w2 = w * w;
-          ax[0] = __builtin_fmaf(w2, dx, ax[0]);
-          ay[0] = __builtin_fmaf(w2, dy, ay[0]);
-        }
-      }
-      if (FORCES) {
-        hx += (ax[0] + ax[1]) + (ax[2] + ax[3]);
-        hy += (ay[0] + ay[1]) + (ay[2] + ay[3]);
-      }
-      const float zc = (az[0] + az[1]) + (az[2] + az[3]);
-      if (SPLIT) z64 += (double)zc; else z32 += zc;
+    reg_pair h = reg_pair{0.f, 0.f};
+    for (int q = 0; q * kWave < valid; ++q) {
+      const int jl = q * kWave + lane;
+      const float2 v = jl < valid ? Ya[jl] : make_float2(0.f, 0.f);
+      wave_lds_fence();
+      cols[lane] = v;
+      wave_lds_fence();
+      const int count = min(kWave, valid - q * kWave);
+      const float zc = q == r ? diag_chunk<true, FORCES>(yi, cols, count, lane, h)
+                              : diag_chunk<false, FORCES>(yi, cols, count, lane, h);
+      if (SPLIT) z64 += vi ? (double)zc : 0.0; else z32 += vi ? zc : 0.f;
     }
-    if (FORCES && vi) part[((int64_t)a * nb + a) * T + il] = make_float2(hx, hy);
+    if (FORCES && vi) part[((int64_t)a * nb + a) * T + il] = make_float2(h.y, h.x);
   }
-  if (SPLIT) {
-    const double z = wave_sum(z64);
-    if (lane == 0) zpart[item] = z;
-  } else {
-    const float z = wave_sum(z32);
-    if (lane == 0) zpart32[item] = z;
+  const double z = SPLIT ? wave_sum(z64) : (double)wave_sum(z32);
+  if (lane == 0) s_z[wave] = z;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (SPLIT) zpart[item] = (s_z[0] + s_z[1]) + (s_z[2] + s_z[3]);
+    else zpart32[item] = ((float)s_z[0] + (float)s_z[1]) + ((float)s_z[2] + (float)s_z[3]);
   }
+  static_assert(kWavesPerBlock == 4, "the fixed-order combination above adds four sums");
 }
 
 // Waves per SIMD the repulsion kernels must allow: with fewer, two waves'
@@ -404,23 +438,39 @@ constexpr int repulse_min_waves() {
   return R <= 4 ? 8 : R <= 8 ? 6 : R <= 16 ? 4 : 1;
 }
 
+// Workgroups that take one tile per wave; those after them take one of the
+// n_diag diagonal tiles (the first of the list) each.
+__host__ __device__ __forceinline__ int64_t wave_tile_blocks(int64_t n_items, int64_t n_diag) {
+  return (n_items - n_diag + kWavesPerBlock - 1) / kWavesPerBlock;
+}
+
 template <int R, bool SPLIT, bool SYM>
 __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_repulse(const float2* __restrict__ Y, int32_t n, int32_t nb,
-                                                    const int2* __restrict__ items, int64_t n_items,
+                                                    const int2* __restrict__ items, int64_t n_items, int64_t n_diag,
                                                     float2* __restrict__ part, double* __restrict__ zpart,
                                                     float* __restrict__ zpart32) {
-  const int64_t item =
-      (int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  if (item >= n_items) return;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
-  const int2 ab = items[item];
-  const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
-  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
-  float2* cols = s_cols[threadIdx.x >> 6];
   if (SYM) {
-    if (a != b) tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, cols);
-    else tile_diag_light<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, lane);
+    __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+    __shared__ double s_z[kWavesPerBlock];
+    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
+    if ((int64_t)blockIdx.x >= wave_blocks) {
+      const int64_t item = (int64_t)blockIdx.x - wave_blocks;
+      const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
+      tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+      return;
+    }
+    const int64_t item = n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (item >= n_items) return;
+    const int2 ab = items[item];
+    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
+    tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, s_cols[wave]);
   } else {
+    const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (item >= n_items) return;
+    const int2 ab = items[item];
+    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
     tile_direct<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane);
   }
 }
@@ -428,22 +478,32 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_repulse(cons
 // Z alone (no forces, no partials written): the weights and their sums in the
 // order k_repulse uses, so the Z partials are bitwise those of the force pass.
 template <int R, bool SPLIT, bool SYM>
-__global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const float2* __restrict__ Y, int32_t n,
-                                                                          int32_t nb, const int2* __restrict__ items,
-                                                                          int64_t n_items, double* __restrict__ zpart,
-                                                                          float* __restrict__ zpart32) {
-  const int64_t item =
-      (int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  if (item >= n_items) return;
+__global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const float2* __restrict__ Y, int32_t n, int32_t nb,
+                                                    const int2* __restrict__ items, int64_t n_items, int64_t n_diag,
+                                                    double* __restrict__ zpart,
+                                                    float* __restrict__ zpart32) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
-  const int2 ab = items[item];
-  const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
-  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
-  float2* cols = s_cols[threadIdx.x >> 6];
   if (SYM) {
-    if (a != b) tile_symmetric<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane, cols);
-    else tile_diag_light<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, lane);
+    __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+    __shared__ double s_z[kWavesPerBlock];
+    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
+    if ((int64_t)blockIdx.x >= wave_blocks) {
+      const int64_t item = (int64_t)blockIdx.x - wave_blocks;
+      const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
+      tile_diag<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+      return;
+    }
+    const int64_t item = n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (item >= n_items) return;
+    const int2 ab = items[item];
+    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
+    tile_symmetric<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane, s_cols[wave]);
   } else {
+    const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (item >= n_items) return;
+    const int2 ab = items[item];
+    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
     tile_direct<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane);
   }
 }
@@ -451,20 +511,20 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
 template <int R>
 hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)((p.items + kWavesPerBlock - 1) / kWavesPerBlock));
+  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag) + p.diag));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
-    hipLaunchKernelGGL((k_zonly<R, true, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.zpart,
+    hipLaunchKernelGGL((k_zonly<R, true, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.zpart,
                        ws.zpart32);
   else if (split)
-    hipLaunchKernelGGL((k_zonly<R, true, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.zpart,
+    hipLaunchKernelGGL((k_zonly<R, true, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.zpart,
                        ws.zpart32);
   else if (sym)
-    hipLaunchKernelGGL((k_zonly<R, false, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.zpart,
+    hipLaunchKernelGGL((k_zonly<R, false, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.zpart,
                        ws.zpart32);
   else
-    hipLaunchKernelGGL((k_zonly<R, false, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items,
+    hipLaunchKernelGGL((k_zonly<R, false, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag,
                        ws.zpart, ws.zpart32);
   return hipGetLastError();
 }
@@ -472,20 +532,20 @@ hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int p
 template <int R>
 hipError_t launch_repulsion_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)((p.items + kWavesPerBlock - 1) / kWavesPerBlock));
+  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag) + p.diag));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
-    hipLaunchKernelGGL((k_repulse<R, true, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.part,
+    hipLaunchKernelGGL((k_repulse<R, true, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.part,
                        ws.zpart, ws.zpart32);
   else if (split)
-    hipLaunchKernelGGL((k_repulse<R, true, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.part,
+    hipLaunchKernelGGL((k_repulse<R, true, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.part,
                        ws.zpart, ws.zpart32);
   else if (sym)
-    hipLaunchKernelGGL((k_repulse<R, false, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, ws.part,
+    hipLaunchKernelGGL((k_repulse<R, false, true>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag, ws.part,
                        ws.zpart, ws.zpart32);
   else
-    hipLaunchKernelGGL((k_repulse<R, false, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items,
+    hipLaunchKernelGGL((k_repulse<R, false, false>), grid, dim3(kBlock), 0, s, Y, n, p.nb, ws.items, p.items, p.diag,
                        ws.part, ws.zpart, ws.zpart32);
   return hipGetLastError();
 }
@@ -747,21 +807,24 @@ __device__ __forceinline__ bool batch_live(const BatchDesc& d) {
 
 template <int R, bool SPLIT>
 __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_repulse(const BatchDesc* __restrict__ descs,
-                                                          const int4* __restrict__ items, int64_t n_items) {
-  const int64_t item =
-      (int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+                                                          const int4* __restrict__ items, int64_t n_items,
+                                                          int64_t n_diag) {
+  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  __shared__ double s_z[kWavesPerBlock];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
+  const bool diag = (int64_t)blockIdx.x >= wave_blocks;
+  const int64_t item = diag ? (int64_t)blockIdx.x - wave_blocks : n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
   if (item >= n_items) return;
   const int4 it = items[item];
   const int32_t gi = __builtin_amdgcn_readfirstlane(it.x);
   const BatchDesc& d = descs[gi];
   if (!batch_live(d)) return;
-  const int lane = threadIdx.x & (kWave - 1);
   const int32_t a = __builtin_amdgcn_readfirstlane(it.y), b = __builtin_amdgcn_readfirstlane(it.z);
   const int64_t li = __builtin_amdgcn_readfirstlane(it.w);
-  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
-  float2* cols = s_cols[threadIdx.x >> 6];
-  if (a != b) tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane, cols);
-  else tile_diag_light<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, li, lane);
+  if (diag) tile_diag<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, li, wave, lane, s_cols[wave], s_z);
+  else tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane, s_cols[wave]);
 }
 
 template <bool SPLIT>
@@ -940,6 +1003,7 @@ RepulsionPlan make_plan(int32_t n, int32_t R, int32_t variant) {
   p.T = kWave * R;
   p.nb = (n + p.T - 1) / p.T;
   p.items = items_for(R);
+  p.diag = p.variant == TSGNE_REPULSION_SYMMETRIC ? p.nb : 0;
   return p;
 }
 
@@ -1041,11 +1105,13 @@ hipError_t launch_kl_ws(const tsgne_graph* g, const Workspace& ws, const float2*
 
 template <int R>
 hipError_t launch_batch_repulse_r(const BatchPlan& bp, bool split, hipStream_t s) {
-  const dim3 grid((unsigned)((bp.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
+  const dim3 grid((unsigned)(wave_tile_blocks(bp.n_items, bp.n_diag) + bp.n_diag));
   if (split)
-    hipLaunchKernelGGL((k_batch_repulse<R, true>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items);
+    hipLaunchKernelGGL((k_batch_repulse<R, true>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items,
+                       bp.n_diag);
   else
-    hipLaunchKernelGGL((k_batch_repulse<R, false>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items);
+    hipLaunchKernelGGL((k_batch_repulse<R, false>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items,
+                       bp.n_diag);
   return hipGetLastError();
 }
 
