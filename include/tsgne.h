@@ -388,9 +388,9 @@ TSGNE_API tsgne_status tsgne_step(tsgne_graph* g, float* Y_d, float* upd_d, floa
  * n_iter steps t = 0 .. n_iter-1 from the layout in Y_d (float32[n][2], in:
  * Y0, out: final layout), with internal upd (0) and gains (1): the loop that
  * minimises eq. (5).  Equals n_iter calls of tsgne_step bit for bit.  The
- * steps are captured once as a HIP graph of up to 32 steps (the step index
- * lives on the device, which switches exaggeration and momentum at
- * exaggeration_iters) and replayed on `stream`; the host does not touch the
+ * steps are queued on `stream` one after the other (the step index lives on
+ * the device, which switches exaggeration and momentum at
+ * exaggeration_iters); the host does not touch the
  * layout between steps.  If p->kl_every > 0 and kl_trace_h is not NULL,
  * kl_trace_h[k] receives the KL (eq. (5), unexaggerated P) after step
  * (k+1)*kl_every - 1, for k < n_iter / kl_every: computed inside the next

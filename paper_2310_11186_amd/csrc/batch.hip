@@ -16,7 +16,6 @@
 
 namespace tsgne {
 
-constexpr int kBatchBlockRows = 256;  // rows per update block
 constexpr int kBatchAttractRows = 256 / kAttractRowLanes;  // rows per attraction block
 
 BatchRun::~BatchRun() {
@@ -53,6 +52,8 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
     d.attract = ws.attract;
     d.t = m[k].t;
     d.limit = m[k].limit;
+    d.t_run = nullptr;  // set with the tables below
+    bp_.max_items = std::max(bp_.max_items, ws.plan.items);
     d.n_items = ws.plan.items;
     d.n = g->n;
     d.nb = ws.plan.nb;
@@ -69,7 +70,7 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
     }
     for (int32_t a = 0; a < nb - 1; ++a, ++li) last_items.push_back(make_int4(k, a, nb - 1, (int)li));
     for (int32_t r = 0; r < g->n; r += kBatchAttractRows) chunks.push_back(make_int2(k, r));
-    for (int32_t r = 0; r < g->n; r += kBatchBlockRows) blocks.push_back(make_int2(k, r));
+    for (int32_t r = 0; r < g->n; r += kUpdateBlockRows) blocks.push_back(make_int2(k, r));
     if (g->n_heavy > 0) {
       std::vector<int32_t> h((size_t)g->n_heavy);
       TSGNE_HIP(hipMemcpy(h.data(), g->heavy, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost), "read heavy rows");
@@ -92,7 +93,8 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
   const size_t b_heavy = sizeof(int2) * heavy.size();
   const size_t b_blocks = sizeof(int2) * blocks.size();
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t total = up(b_descs) + up(b_items) + up(b_chunks) + up(b_heavy) + up(b_blocks);
+  const size_t b_run = sizeof(int32_t) * (size_t)count;
+  const size_t total = up(b_descs) + up(b_items) + up(b_chunks) + up(b_heavy) + up(b_blocks) + up(b_run);
   if (tables_) (void)hipFree(tables_);
   tables_ = nullptr;
   TSGNE_HIP(hipMalloc(&tables_, total), "allocate batch tables");
@@ -108,6 +110,8 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
   bp_.light_chunks = reinterpret_cast<int2*>(place(b_chunks));
   bp_.heavy = reinterpret_cast<int2*>(place(b_heavy));
   bp_.row_blocks = reinterpret_cast<int2*>(place(b_blocks));
+  int32_t* t_run = reinterpret_cast<int32_t*>(place(b_run));  // written by each step's forces before it is read
+  for (int32_t k = 0; k < count; ++k) descs[(size_t)k].t_run = t_run + k;
   TSGNE_HIP(hipMemcpy(bp_.descs, descs.data(), b_descs, hipMemcpyHostToDevice), "upload batch descriptors");
   if (b_items) TSGNE_HIP(hipMemcpy(bp_.items, diag_items.data(), b_items, hipMemcpyHostToDevice), "upload items");
   if (b_chunks) TSGNE_HIP(hipMemcpy(bp_.light_chunks, chunks.data(), b_chunks, hipMemcpyHostToDevice), "upload rows");

@@ -20,6 +20,8 @@ constexpr int32_t kHeavyDegree = 64;
 // Lanes per row in the attraction of rows up to kHeavyDegree entries (the
 // single-graph and batched kernels must agree: it fixes the summation order).
 constexpr int kAttractRowLanes = 8;
+// Rows per workgroup of the batched update.
+constexpr int kUpdateBlockRows = 64;
 
 // Bits of the device error word written by the CSR check.
 enum : uint32_t {
@@ -56,7 +58,7 @@ struct Workspace {
   int32_t kl_blocks = 0;
 };
 
-// The early-exaggeration schedule read on the device by a replayed step
+// The early-exaggeration schedule read on the device by a step of a run
 // (tstep == nullptr: the host passes alpha and the momentum instead).
 struct StepSchedule {
   const int32_t* tstep = nullptr;
@@ -80,6 +82,7 @@ struct BatchDesc {
   double* Z;
   double2* attract;
   int32_t* t;        // this graph's step index (advanced after every step)
+  int32_t* t_run;    // the index after the step being run, -1 if there is none
   const int32_t* limit;  // steps run only while t < limit (a round's allotment)
   int64_t n_items;
   int32_t n;
@@ -94,9 +97,10 @@ struct BatchPlan {
   int4* items = nullptr;          // (graph, a, b, item index within the graph), diagonal tiles first
   int2* light_chunks = nullptr;   // (graph, first row) per 32-row block
   int2* heavy = nullptr;          // (graph, row) per heavy row
-  int2* row_blocks = nullptr;     // (graph, first row) per 256-row block
+  int2* row_blocks = nullptr;     // (graph, first row) per kUpdateBlockRows rows
   int64_t n_items = 0;
   int64_t n_diag = 0;
+  int64_t max_items = 0;          // most tiles of one graph
   int32_t n_light_chunks = 0;
   int32_t n_heavy = 0;
   int32_t n_row_blocks = 0;
@@ -267,12 +271,17 @@ hipError_t launch_repulsion(const Workspace& ws, int32_t n, const float2* Y, int
 // Z partials only (the repulsion's tiles without forces): bitwise the Z the
 // force pass gives at the same Y and plan; partial forces untouched.
 hipError_t launch_zonly(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s);
-// tstep (nullable): advance a run's device step counter (see Workspace::tstep).
+// Repulsion and attraction in one launch (symmetric plans only); tstep
+// (nullable): advance a run's device step counter (see Workspace::tstep).
+hipError_t launch_forces(const tsgne_graph* g, const float2* Y, int precision, int32_t* tstep, hipStream_t s);
+// Whether the update after launch_forces sums Z itself (own_z).
+bool plan_fuses_z(const RepulsionPlan& plan);
+// tstep (nullable): as launch_forces.
 hipError_t launch_zsum(const Workspace& ws, int precision, hipStream_t s, int32_t* tstep = nullptr);
 hipError_t launch_attract(const tsgne_graph* g, const float2* Y, int precision, double2* out, hipStream_t s);
 hipError_t launch_update(const tsgne_graph* g, float2* Y, float2* U, float2* gains, float alpha, float momentum,
                          float eta, float min_gain, int precision, bool do_update, float2* grad_out, double* Z_out,
-                         hipStream_t s, const StepSchedule& sched = StepSchedule{});
+                         bool own_z, hipStream_t s, const StepSchedule& sched = StepSchedule{});
 // KL at Y with the Z in the workspace into klout; inside a run (tstep set)
 // only on sampled steps, also into trace (see k_kl_final); with tstep null and
 // trace set, also into trace[0].
@@ -281,6 +290,8 @@ hipError_t launch_kl(const tsgne_graph* g, const float2* Y, hipStream_t s, const
 // KL of g's P at Y with the Z, partials and output of a given workspace view
 // (ws.Z, ws.klpart[ws.kl_blocks], ws.klout).
 hipError_t launch_kl_ws(const tsgne_graph* g, const Workspace& ws, const float2* Y, hipStream_t s);
+// Start of a run: U = 0, gains = 1, the step counter and the flag 0.
+hipError_t launch_run_init(float2* U, float2* gains, int32_t n, int32_t* tstep, uint32_t* flag, hipStream_t s);
 hipError_t launch_nonfinite_check(const float2* Y, int32_t n, uint32_t* flag, hipStream_t s);
 hipError_t launch_batch_step(const BatchPlan& bp, const tsgne_params& p, hipStream_t s);
 

@@ -709,15 +709,166 @@ __global__ __launch_bounds__(kBlock) void k_attract_heavy(const int32_t* __restr
   attract_row<kWave, SPLIT>(row_ptr, col, P, Y, heavy[w], (int)(threadIdx.x & (kWave - 1)), out);
 }
 
-// g_i = 4 (alpha * A_i - R_i / Z), then the momentum/gains update of row i.
-template <bool SPLIT>
-__device__ __forceinline__ void update_row(const float2* __restrict__ part, int32_t nb, int32_t T,
-                                           const double2* __restrict__ attract, double Z, int32_t i,
-                                           float2* __restrict__ Y, float2* __restrict__ U, float2* __restrict__ G,
-                                           float alpha, float momentum, float eta, float min_gain, bool do_update,
-                                           float2* __restrict__ grad_out) {
-  const int32_t k = i / T, off = i - k * T;
-  const float2* __restrict__ pp = part + (int64_t)k * nb * T + off;
+// Workgroups of the attraction inside a launch of the repulsion, so that their
+// loads' latency passes while tiles are computed beside them.  Workgroups are
+// dealt to the XCDs in turn and inside each to its 32 compute units in turn,
+// so the unit is one per XCD, every stride-th group of kXcds workgroups is the
+// attraction's, and stride is odd: with every second one its, half of the
+// compute units got no tile at all (104 us a launch at 20,000 nodes, 64 us for
+// the tiles alone).  With stride 1 the attraction goes first.
+struct AttractBlocks {
+  uint32_t light = 0, heavy = 0;  // workgroups with work
+  uint32_t groups = 0;            // groups of kXcds
+  uint32_t stride = 1;
+};
+
+AttractBlocks mix_attract(int64_t tile_blocks, int64_t light, int64_t heavy) {
+  AttractBlocks m;
+  m.light = (uint32_t)light;
+  m.heavy = (uint32_t)heavy;
+  m.groups = (uint32_t)((light + heavy + kXcds - 1) / kXcds);
+  if (m.groups > 0) m.stride = ((uint32_t)((tile_blocks / kXcds + m.groups) / m.groups) - 1) | 1;
+  return m;
+}
+
+unsigned mixed_grid(int64_t tile_blocks, const AttractBlocks& m) {
+  return (unsigned)(tile_blocks + (int64_t)m.groups * kXcds);
+}
+
+// Which workgroup of the launch this is: >= 0 its index among the
+// attraction's (which may lie past its last one), otherwise -1 - its index
+// among the tiles'.
+__device__ __forceinline__ int64_t mixed_block(const AttractBlocks& m) {
+  const uint32_t i = blockIdx.x, group = i / kXcds, q = group / m.stride;
+  if (q < m.groups && group - q * m.stride == m.stride - 1) return (int64_t)q * kXcds + i % kXcds;
+  return -1 - (int64_t)(i - min(q, m.groups) * kXcds);
+}
+
+// The forces at Y in one launch: the tiles of a symmetric plan (as k_repulse)
+// and the attraction (as k_attract_light and _heavy), which needs nothing of
+// them.  tstep (nullable): a run's device step counter {next step, step being
+// run}, advanced here for the kernels after this one.  At 2,000 nodes a step
+// was four launches of 5.5, 2.7, 2.7 and 5.5 us, mostly latency.
+template <int R, bool SPLIT>
+__global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_forces(
+    const float2* __restrict__ Y, int32_t n, int32_t nb, const int2* __restrict__ items, int64_t n_items,
+    int64_t n_diag, float2* __restrict__ part, double* __restrict__ zpart, float* __restrict__ zpart32,
+    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const float* __restrict__ P,
+    const int32_t* __restrict__ heavy, int32_t n_heavy, double2* __restrict__ attract, AttractBlocks mix,
+    int32_t* __restrict__ tstep) {
+  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  __shared__ double s_z[kWavesPerBlock];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & (kWave - 1);
+  if (tstep && blockIdx.x == 0 && threadIdx.x == 0) {
+    const int32_t t = tstep[0];
+    tstep[1] = t;
+    tstep[0] = t + 1;
+  }
+  const int64_t mixed = mixed_block(mix);
+  if (mixed >= 0) {
+    if (mixed < mix.light) {
+      const int32_t i0 = (int32_t)(mixed * (kBlock / kRowLanes) + threadIdx.x / kRowLanes);
+      const int32_t i = min(i0, n - 1);
+      // whole 8-lane groups take the branch together, so the shuffles inside stay in step
+      if (i0 < n && row_ptr[i + 1] - row_ptr[i] <= kHeavyDegree)
+        attract_row<kRowLanes, SPLIT>(row_ptr, col, P, Y, i, (int)(threadIdx.x & (kRowLanes - 1)), attract);
+    } else {
+      const int32_t w = (int32_t)(mixed - mix.light) * kWavesPerBlock + wave;
+      if (w < n_heavy) attract_row<kWave, SPLIT>(row_ptr, col, P, Y, heavy[w], lane, attract);
+    }
+    return;
+  }
+  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag);
+  if (block >= wave_blocks) {
+    const int64_t item = block - wave_blocks;
+    const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
+    tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+    return;
+  }
+  const int64_t item = n_diag + block * kWavesPerBlock + wave;
+  if (item >= n_items) return;
+  const int2 ab = items[item];
+  const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
+  tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, s_cols[wave]);
+}
+
+// Plans of at most this many tiles have their Z summed by every workgroup of
+// the update for itself (see block_Z) instead of by a kernel of its own: up to
+// here the 64 KB of partials are read from L2 in the shadow of the force
+// partials' loads, and a launch is saved.
+constexpr int64_t kOwnZItems = 8192;
+constexpr int kUpdateRows = kUpdateBlockRows;  // rows per workgroup of the update
+static_assert(kUpdateRows == kWave, "one row per lane");
+
+// Z of at most kOwnZItems tile partials by a workgroup of kBlock threads, to
+// every thread: the additions of zsum_block in its order, each thread standing
+// for four of its 1024, so bitwise the same Z.
+template <typename V>
+__device__ __forceinline__ V block_Z(const V* __restrict__ zpart, int32_t n_items, V* s_z) {
+  constexpr int kPer = kZThreads / kBlock, kLoads = (int)(kOwnZItems / kZThreads);
+  static_assert(kPer == 4 && kLoads == 8, "the combinations below add four threads' sums of eight loads");
+  const int t = threadIdx.x;
+  V a[kPer];
+#pragma unroll
+  for (int p = 0; p < kPer; ++p) {
+    V v[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int32_t k = t + p * kBlock + u * kZThreads;
+      v[u] = u * kZThreads < n_items ? zpart[min(k, n_items - 1)] : (V)0;
+      v[u] = k < n_items ? v[u] : (V)0;
+    }
+    a[p] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+  }
+  V z = (a[0] + a[2]) + (a[1] + a[3]);  // the tree's levels 512 and 256
+  s_z[t] = z;
+  __syncthreads();
+  if (t < kWave) {
+    z = s_z[t] + s_z[t + 2 * kWave];
+    z += s_z[t + kWave] + s_z[t + 3 * kWave];
+    for (int w = kWave / 2; w > 0; w >>= 1) z += __shfl_down(z, w, kWave);
+    if (t == 0) s_z[0] = z;
+  }
+  __syncthreads();
+  return s_z[0];
+}
+
+// What the update needs of one graph.
+struct UpdateView {
+  const float2* part;
+  const double2* attract;
+  const double* zpart;
+  const float* zpart32;
+  double* Z;  // read, or written by the first workgroup where it sums Z itself
+  float2* Y;
+  float2* U;
+  float2* G;
+  int32_t n, nb, n_items;
+};
+
+// g_i = 4 (alpha * A_i - R_i / Z) and the momentum/gains update of rows
+// i0 .. i0 + 63, one row per lane.  Each wave of the workgroup sums a
+// contiguous quarter of the rows' force partials in block order (FP64 in the
+// split mode), the quarters are added in order, and the first wave finishes.
+// Bound by latency for small graphs (a chain of loads and sums) and by the
+// partials' 8 n nb bytes for large ones; four waves per 64 rows keep four
+// times the loads in flight that a wave per 64 rows did.
+template <bool SPLIT, bool OWN_Z>
+__device__ __forceinline__ void update_rows(const UpdateView& v, int32_t T, int32_t i0, float alpha, float momentum,
+                                            float eta, float min_gain, bool do_update, float2* __restrict__ grad_out,
+                                            double* __restrict__ Z_out) {
+  __shared__ double2 s_r[kWavesPerBlock][kWave];
+  __shared__ double s_z[kBlock];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & (kWave - 1);
+  const int32_t i = i0 + lane;
+  // a row block holds whole groups of 64 rows; rows past n read the partial
+  // buffer inside their own row block and store nothing
+  const int32_t k = i0 / T;
+  const float2* __restrict__ pp = v.part + (int64_t)k * v.nb * T + (i0 - k * T) + lane;
+  const int32_t quarter = (v.nb + kWavesPerBlock - 1) / kWavesPerBlock;
+  const int32_t first = wave * quarter, end = min(v.nb, first + quarter);
   double rx = 0.0, ry = 0.0;
   float sx = 0.f, sy = 0.f;
   // Partials are read in batches of kBatchLoads whose loads are all issued
@@ -725,26 +876,52 @@ __device__ __forceinline__ void update_row(const float2* __restrict__ part, int3
   // a load makes the compiler wait for it before the next one is issued), so
   // past the last block an index is clamped to it: an in-bounds re-read that
   // adds +0, which leaves a sum started at +0 unchanged.
-  constexpr int kBatchLoads = 32;
-  for (int32_t o0 = 0; o0 < nb; o0 += kBatchLoads) {
-    float2 v[kBatchLoads];
+  constexpr int kBatchLoads = 16;
+  for (int32_t o0 = first; o0 < end; o0 += kBatchLoads) {
+    float2 p[kBatchLoads];
 #pragma unroll
-    for (int u = 0; u < kBatchLoads; ++u) v[u] = pp[(int64_t)min(o0 + u, nb - 1) * T];
-    // added in block order, exactly as a one-at-a-time loop
-    const int32_t count = nb - o0;
+    for (int u = 0; u < kBatchLoads; ++u) p[u] = pp[(int64_t)min(o0 + u, end - 1) * T];
+    const int32_t count = end - o0;
 #pragma unroll
     for (int u = 0; u < kBatchLoads; ++u) {
       const bool in = u < count;
       if (SPLIT) {
-        rx += in ? (double)v[u].x : 0.0;
-        ry += in ? (double)v[u].y : 0.0;
+        rx += in ? (double)p[u].x : 0.0;
+        ry += in ? (double)p[u].y : 0.0;
       } else {
-        sx += in ? v[u].x : 0.f;
-        sy += in ? v[u].y : 0.f;
+        sx += in ? p[u].x : 0.f;
+        sy += in ? p[u].y : 0.f;
       }
     }
   }
-  const double2 A = attract[i];
+  s_r[wave][lane] = SPLIT ? make_double2(rx, ry) : make_double2(sx, sy);
+  double Z;
+  if (OWN_Z) {
+    Z = SPLIT ? block_Z<double>(v.zpart, v.n_items, s_z)
+              : (double)block_Z<float>(v.zpart32, v.n_items, reinterpret_cast<float*>(s_z));
+  } else {
+    Z = *v.Z;
+    __syncthreads();
+  }
+  if (i0 == 0 && threadIdx.x == 0) {
+    if (OWN_Z) *v.Z = Z;
+    if (Z_out) *Z_out = Z;
+  }
+  if (wave != 0 || i >= v.n) return;
+  rx = sx = 0.f;
+  ry = sy = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    const double2 r = s_r[w][lane];
+    if (SPLIT) {
+      rx += r.x;
+      ry += r.y;
+    } else {
+      sx += (float)r.x;
+      sy += (float)r.y;
+    }
+  }
+  const double2 A = v.attract[i];
   float2 g;
   if (SPLIT) {
     const double invZ = Z > 0.0 ? 1.0 / Z : 0.0;
@@ -757,7 +934,7 @@ __device__ __forceinline__ void update_row(const float2* __restrict__ part, int3
   }
   if (grad_out) grad_out[i] = g;
   if (!do_update) return;
-  float2 y = Y[i], u = U[i], gn = G[i];
+  float2 y = v.Y[i], u = v.U[i], gn = v.G[i];
   gn.x = (g.x * u.x < 0.f) ? gn.x + 0.2f : gn.x * 0.8f;
   gn.y = (g.y * u.y < 0.f) ? gn.y + 0.2f : gn.y * 0.8f;
   gn.x = fmaxf(gn.x, min_gain);
@@ -766,29 +943,25 @@ __device__ __forceinline__ void update_row(const float2* __restrict__ part, int3
   u.y = momentum * u.y - eta * gn.y * g.y;
   y.x += u.x;
   y.y += u.y;
-  Y[i] = y;
-  U[i] = u;
-  G[i] = gn;
+  v.Y[i] = y;
+  v.U[i] = u;
+  v.G[i] = gn;
 }
 
 // With sched.tstep set, alpha and the momentum come from the step index on the
-// device (early exaggeration while t < t_ee), so that a captured step can be
-// replayed; otherwise the host's values are used.
-template <bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_update(const float2* __restrict__ part, int32_t nb, int32_t T,
-                                                   const double2* __restrict__ attract, const double* __restrict__ Zp,
-                                                   int32_t n, float2* __restrict__ Y, float2* __restrict__ U,
-                                                   float2* __restrict__ G, float alpha, float momentum, float eta,
+// device (early exaggeration while t < t_ee); otherwise the host's values are
+// used.
+template <bool SPLIT, bool OWN_Z>
+__global__ __launch_bounds__(kBlock) void k_update(UpdateView v, int32_t T, float alpha, float momentum, float eta,
                                                    float min_gain, int do_update, float2* __restrict__ grad_out,
-                                                   StepSchedule sched) {
-  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+                                                   double* __restrict__ Z_out, StepSchedule sched) {
   if (sched.tstep) {
     const bool early = sched.tstep[1] < sched.exaggeration_iters;
     alpha = early ? sched.early_exaggeration : 1.0f;
     momentum = early ? sched.momentum_early : sched.momentum_late;
   }
-  update_row<SPLIT>(part, nb, T, attract, *Zp, i, Y, U, G, alpha, momentum, eta, min_gain, do_update != 0, grad_out);
+  update_rows<SPLIT, OWN_Z>(v, T, (int32_t)blockIdx.x * kUpdateRows, alpha, momentum, eta, min_gain, do_update != 0,
+                            grad_out, Z_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -800,29 +973,54 @@ __global__ __launch_bounds__(kBlock) void k_update(const float2* __restrict__ pa
 // can share a launch; graphs with t >= n_iter are skipped.
 // ---------------------------------------------------------------------------
 
+// A graph's step index is kept twice, so that no launch reads what it writes:
+// the forces read t and leave t + 1 in t_run (-1 where the graph has no step
+// to take), the update reads t_run and leaves it in t.
 __device__ __forceinline__ bool batch_live(const BatchDesc& d) {
   const int32_t t = *d.t;
   return t < d.n_iter && t < *d.limit;
 }
 
+// The forces of every live graph in one launch, as k_forces.
 template <int R, bool SPLIT>
-__global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_repulse(const BatchDesc* __restrict__ descs,
-                                                          const int4* __restrict__ items, int64_t n_items,
-                                                          int64_t n_diag) {
+__global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_forces(
+    const BatchDesc* __restrict__ descs, const int4* __restrict__ items, int64_t n_items, int64_t n_diag,
+    const int2* __restrict__ chunks, const int2* __restrict__ heavy, int32_t n_heavy, AttractBlocks mix) {
   __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
   __shared__ double s_z[kWavesPerBlock];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
-  const bool diag = (int64_t)blockIdx.x >= wave_blocks;
-  const int64_t item = diag ? (int64_t)blockIdx.x - wave_blocks : n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
+  const int64_t mixed = mixed_block(mix);
+  if (mixed >= 0) {
+    if (mixed < mix.light) {  // kBlock / kRowLanes light rows of one graph
+      const int2 ch = chunks[mixed];
+      const BatchDesc& d = descs[ch.x];
+      if (!batch_live(d)) return;
+      const int32_t i0 = ch.y + (int32_t)(threadIdx.x / kRowLanes);
+      const int32_t i = min(i0, d.n - 1);
+      if (i0 < d.n && d.row_ptr[i + 1] - d.row_ptr[i] <= kHeavyDegree)
+        attract_row<kRowLanes, SPLIT>(d.row_ptr, d.col, d.P, d.Y, i, (int)(threadIdx.x & (kRowLanes - 1)), d.attract);
+    } else {
+      const int32_t w = (int32_t)(mixed - mix.light) * kWavesPerBlock + wave;
+      if (w >= n_heavy) return;
+      const int2 hr = heavy[w];
+      const BatchDesc& d = descs[hr.x];
+      if (batch_live(d)) attract_row<kWave, SPLIT>(d.row_ptr, d.col, d.P, d.Y, hr.y, lane, d.attract);
+    }
+    return;
+  }
+  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag);
+  const bool diag = block >= wave_blocks;
+  const int64_t item = diag ? block - wave_blocks : n_diag + block * kWavesPerBlock + wave;
   if (item >= n_items) return;
   const int4 it = items[item];
   const int32_t gi = __builtin_amdgcn_readfirstlane(it.x);
   const BatchDesc& d = descs[gi];
-  if (!batch_live(d)) return;
   const int32_t a = __builtin_amdgcn_readfirstlane(it.y), b = __builtin_amdgcn_readfirstlane(it.z);
   const int64_t li = __builtin_amdgcn_readfirstlane(it.w);
+  const bool live = batch_live(d);
+  if (diag && a == 0 && threadIdx.x == 0) *d.t_run = live ? *d.t + 1 : -1;
+  if (!live) return;
   if (diag) tile_diag<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, li, wave, lane, s_cols[wave], s_z);
   else tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane, s_cols[wave]);
 }
@@ -830,54 +1028,24 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_repuls
 template <bool SPLIT>
 __global__ __launch_bounds__(kZThreads) void k_batch_zsum(const BatchDesc* __restrict__ descs) {
   const BatchDesc& d = descs[blockIdx.x];
-  if (!batch_live(d)) return;
+  if (*d.t_run < 0) return;
   zsum_block<SPLIT>(d.zpart, d.zpart32, d.n_items, d.Z);
 }
 
-// One block of 256 threads covers kBlock / kRowLanes light rows of one graph.
-template <bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_batch_attract_light(const BatchDesc* __restrict__ descs,
-                                                                const int2* __restrict__ chunks) {
-  const int2 ch = chunks[blockIdx.x];
-  const BatchDesc& d = descs[ch.x];
-  if (!batch_live(d)) return;
-  const int32_t i0 = ch.y + (int32_t)(threadIdx.x / kRowLanes);
-  const int32_t i = min(i0, d.n - 1);
-  const bool live = i0 < d.n && (d.row_ptr[i + 1] - d.row_ptr[i]) <= kHeavyDegree;
-  if (live) attract_row<kRowLanes, SPLIT>(d.row_ptr, d.col, d.P, d.Y, i, (int)(threadIdx.x & (kRowLanes - 1)),
-                                          d.attract);
-}
-
-template <bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_batch_attract_heavy(const BatchDesc* __restrict__ descs,
-                                                                const int2* __restrict__ heavy, int32_t n_heavy) {
-  const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
-  if (w >= n_heavy) return;
-  const int2 hr = heavy[w];
-  const BatchDesc& d = descs[hr.x];
-  if (!batch_live(d)) return;
-  attract_row<kWave, SPLIT>(d.row_ptr, d.col, d.P, d.Y, hr.y, (int)(threadIdx.x & (kWave - 1)), d.attract);
-}
-
-// One block of 256 threads covers 256 rows of one graph.
-template <bool SPLIT>
+// One workgroup covers kUpdateRows rows of one graph.
+template <bool SPLIT, bool OWN_Z>
 __global__ __launch_bounds__(kBlock) void k_batch_update(const BatchDesc* __restrict__ descs,
                                                          const int2* __restrict__ blocks, int32_t T, float ee,
                                                          int32_t t_ee, float m_early, float m_late, float min_gain) {
   const int2 bl = blocks[blockIdx.x];
   const BatchDesc& d = descs[bl.x];
-  if (!batch_live(d)) return;
-  const int32_t t = *d.t;
-  const int32_t i = bl.y + (int32_t)threadIdx.x;
-  if (i >= d.n) return;
-  const bool early = t < t_ee;
-  update_row<SPLIT>(d.part, d.nb, T, d.attract, *d.Z, i, d.Y, d.U, d.G, early ? ee : 1.0f, early ? m_early : m_late,
-                    d.eta, min_gain, true, nullptr);
-}
-
-__global__ __launch_bounds__(kBlock) void k_batch_advance(const BatchDesc* __restrict__ descs, int32_t count) {
-  const int32_t g = blockIdx.x * kBlock + threadIdx.x;
-  if (g < count && batch_live(descs[g])) *descs[g].t += 1;
+  const int32_t next = *d.t_run;
+  if (next < 0) return;
+  if (bl.y == 0 && threadIdx.x == 0) *d.t = next;
+  const bool early = next - 1 < t_ee;
+  const UpdateView v{d.part, d.attract, d.zpart, d.zpart32, d.Z, d.Y, d.U, d.G, d.n, d.nb, (int32_t)d.n_items};
+  update_rows<SPLIT, OWN_Z>(v, T, bl.y, early ? ee : 1.0f, early ? m_early : m_late, d.eta, min_gain, true, nullptr,
+                            nullptr);
 }
 
 // KL = sum_e P_e log(P_e / q_e), q_e = w_e / Z, in FP64: fixed grid, strided
@@ -945,6 +1113,18 @@ __global__ __launch_bounds__(kBlock) void k_nonfinite(const float2* __restrict__
   if (i >= n) return;
   const float2 y = Y[i];
   if (!isfinite(y.x) || !isfinite(y.y)) atomicOr(flag, 1u);
+}
+
+__global__ __launch_bounds__(kBlock) void k_run_init(float2* __restrict__ U, float2* __restrict__ gains, int32_t n,
+                                                     int32_t* __restrict__ tstep, uint32_t* __restrict__ flag) {
+  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i == 0) {
+    tstep[0] = tstep[1] = 0;
+    *flag = 0;
+  }
+  if (i >= n) return;
+  U[i] = make_float2(0.f, 0.f);
+  gains[i] = make_float2(1.f, 1.f);
 }
 
 inline unsigned blocks_for(int64_t work, int per) { return (unsigned)((work + per - 1) / per); }
@@ -1065,20 +1245,63 @@ hipError_t launch_attract(const tsgne_graph* g, const float2* Y, int precision, 
   return hipGetLastError();
 }
 
+bool plan_fuses_z(const RepulsionPlan& plan) { return plan.items <= kOwnZItems; }
+
+template <int R>
+hipError_t launch_forces_r(const tsgne_graph* g, const float2* Y, bool split, int32_t* tstep, hipStream_t s) {
+  const Workspace& ws = g->ws;
+  const RepulsionPlan& p = ws.plan;
+  const int64_t tiles = wave_tile_blocks(p.items, p.diag) + p.diag;
+  const AttractBlocks mix = mix_attract(tiles, blocks_for((int64_t)g->n * kRowLanes, kBlock),
+                                        blocks_for(g->n_heavy, kWavesPerBlock));
+  const dim3 grid(mixed_grid(tiles, mix));
+  if (split)
+    hipLaunchKernelGGL((k_forces<R, true>), grid, dim3(kBlock), 0, s, Y, g->n, p.nb, ws.items, p.items, p.diag,
+                       ws.part, ws.zpart, ws.zpart32, g->row_ptr, g->col, g->P, g->heavy, g->n_heavy, ws.attract, mix,
+                       tstep);
+  else
+    hipLaunchKernelGGL((k_forces<R, false>), grid, dim3(kBlock), 0, s, Y, g->n, p.nb, ws.items, p.items, p.diag,
+                       ws.part, ws.zpart, ws.zpart32, g->row_ptr, g->col, g->P, g->heavy, g->n_heavy, ws.attract, mix,
+                       tstep);
+  return hipGetLastError();
+}
+
+hipError_t launch_forces(const tsgne_graph* g, const float2* Y, int precision, int32_t* tstep, hipStream_t s) {
+  const bool split = precision != TSGNE_PREC_FP32;
+  switch (g->ws.plan.R) {
+    case 1: return launch_forces_r<1>(g, Y, split, tstep, s);
+    case 2: return launch_forces_r<2>(g, Y, split, tstep, s);
+    case 4: return launch_forces_r<4>(g, Y, split, tstep, s);
+    case 8: return launch_forces_r<8>(g, Y, split, tstep, s);
+    case 16: return launch_forces_r<16>(g, Y, split, tstep, s);
+    case 12: return launch_forces_r<12>(g, Y, split, tstep, s);
+    case 14: return launch_forces_r<14>(g, Y, split, tstep, s);
+    case 15: return launch_forces_r<15>(g, Y, split, tstep, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_update(const tsgne_graph* g, float2* Y, float2* U, float2* gains, float alpha, float momentum,
                          float eta, float min_gain, int precision, bool do_update, float2* grad_out, double* Z_out,
-                         hipStream_t s, const StepSchedule& sched) {
+                         bool own_z, hipStream_t s, const StepSchedule& sched) {
   const Workspace& ws = g->ws;
-  const unsigned nbk = blocks_for(g->n, kBlock);
-  if (precision == TSGNE_PREC_FP32)
-    hipLaunchKernelGGL(k_update<false>, dim3(nbk), dim3(kBlock), 0, s, ws.part, ws.plan.nb, ws.plan.T, ws.attract,
-                       ws.Z, g->n, Y, U, gains, alpha, momentum, eta, min_gain, (int)do_update, grad_out, sched);
+  const dim3 grid(blocks_for(g->n, kUpdateRows));
+  const bool split = precision != TSGNE_PREC_FP32;
+  const UpdateView v{ws.part, ws.attract, ws.zpart, ws.zpart32, ws.Z, Y, U, gains, g->n, ws.plan.nb,
+                     own_z ? (int32_t)ws.plan.items : 0};
+  if (split && own_z)
+    hipLaunchKernelGGL((k_update<true, true>), grid, dim3(kBlock), 0, s, v, ws.plan.T, alpha, momentum, eta, min_gain,
+                       (int)do_update, grad_out, Z_out, sched);
+  else if (split)
+    hipLaunchKernelGGL((k_update<true, false>), grid, dim3(kBlock), 0, s, v, ws.plan.T, alpha, momentum, eta, min_gain,
+                       (int)do_update, grad_out, Z_out, sched);
+  else if (own_z)
+    hipLaunchKernelGGL((k_update<false, true>), grid, dim3(kBlock), 0, s, v, ws.plan.T, alpha, momentum, eta, min_gain,
+                       (int)do_update, grad_out, Z_out, sched);
   else
-    hipLaunchKernelGGL(k_update<true>, dim3(nbk), dim3(kBlock), 0, s, ws.part, ws.plan.nb, ws.plan.T, ws.attract,
-                       ws.Z, g->n, Y, U, gains, alpha, momentum, eta, min_gain, (int)do_update, grad_out, sched);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !Z_out) return e;
-  return hipMemcpyAsync(Z_out, ws.Z, sizeof(double), hipMemcpyDeviceToDevice, s);
+    hipLaunchKernelGGL((k_update<false, false>), grid, dim3(kBlock), 0, s, v, ws.plan.T, alpha, momentum, eta,
+                       min_gain, (int)do_update, grad_out, Z_out, sched);
+  return hipGetLastError();
 }
 
 hipError_t launch_kl(const tsgne_graph* g, const float2* Y, hipStream_t s, const int32_t* tstep, int32_t kl_every,
@@ -1104,63 +1327,58 @@ hipError_t launch_kl_ws(const tsgne_graph* g, const Workspace& ws, const float2*
 }
 
 template <int R>
-hipError_t launch_batch_repulse_r(const BatchPlan& bp, bool split, hipStream_t s) {
-  const dim3 grid((unsigned)(wave_tile_blocks(bp.n_items, bp.n_diag) + bp.n_diag));
+hipError_t launch_batch_forces_r(const BatchPlan& bp, bool split, hipStream_t s) {
+  const int64_t tiles = wave_tile_blocks(bp.n_items, bp.n_diag) + bp.n_diag;
+  const AttractBlocks mix = mix_attract(tiles, bp.n_light_chunks, blocks_for(bp.n_heavy, kWavesPerBlock));
+  const dim3 grid(mixed_grid(tiles, mix));
   if (split)
-    hipLaunchKernelGGL((k_batch_repulse<R, true>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items,
-                       bp.n_diag);
+    hipLaunchKernelGGL((k_batch_forces<R, true>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items, bp.n_diag,
+                       bp.light_chunks, bp.heavy, bp.n_heavy, mix);
   else
-    hipLaunchKernelGGL((k_batch_repulse<R, false>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items,
-                       bp.n_diag);
+    hipLaunchKernelGGL((k_batch_forces<R, false>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items, bp.n_diag,
+                       bp.light_chunks, bp.heavy, bp.n_heavy, mix);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_step(const BatchPlan& bp, const tsgne_params& p, hipStream_t s) {
   const bool split = p.precision != TSGNE_PREC_FP32;
   hipError_t e = hipSuccess;
-  if (bp.n_items > 0) {
-    switch (bp.R) {
-      case 1: e = launch_batch_repulse_r<1>(bp, split, s); break;
-      case 2: e = launch_batch_repulse_r<2>(bp, split, s); break;
-      case 4: e = launch_batch_repulse_r<4>(bp, split, s); break;
-      case 8: e = launch_batch_repulse_r<8>(bp, split, s); break;
-      case 16: e = launch_batch_repulse_r<16>(bp, split, s); break;
-      case 12: e = launch_batch_repulse_r<12>(bp, split, s); break;
-      case 14: e = launch_batch_repulse_r<14>(bp, split, s); break;
-      case 15: e = launch_batch_repulse_r<15>(bp, split, s); break;
-      default: e = hipErrorInvalidValue;
-    }
-    if (e != hipSuccess) return e;
+  switch (bp.R) {
+    case 1: e = launch_batch_forces_r<1>(bp, split, s); break;
+    case 2: e = launch_batch_forces_r<2>(bp, split, s); break;
+    case 4: e = launch_batch_forces_r<4>(bp, split, s); break;
+    case 8: e = launch_batch_forces_r<8>(bp, split, s); break;
+    case 16: e = launch_batch_forces_r<16>(bp, split, s); break;
+    case 12: e = launch_batch_forces_r<12>(bp, split, s); break;
+    case 14: e = launch_batch_forces_r<14>(bp, split, s); break;
+    case 15: e = launch_batch_forces_r<15>(bp, split, s); break;
+    default: e = hipErrorInvalidValue;
   }
-  if (split) hipLaunchKernelGGL(k_batch_zsum<true>, dim3(bp.count), dim3(kZThreads), 0, s, bp.descs);
-  else hipLaunchKernelGGL(k_batch_zsum<false>, dim3(bp.count), dim3(kZThreads), 0, s, bp.descs);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (bp.n_light_chunks > 0) {
-    if (split)
-      hipLaunchKernelGGL(k_batch_attract_light<true>, dim3(bp.n_light_chunks), dim3(kBlock), 0, s, bp.descs,
-                         bp.light_chunks);
-    else
-      hipLaunchKernelGGL(k_batch_attract_light<false>, dim3(bp.n_light_chunks), dim3(kBlock), 0, s, bp.descs,
-                         bp.light_chunks);
+  if (e != hipSuccess) return e;
+  const bool own_z = bp.max_items <= kOwnZItems;
+  if (!own_z) {
+    if (split) hipLaunchKernelGGL(k_batch_zsum<true>, dim3(bp.count), dim3(kZThreads), 0, s, bp.descs);
+    else hipLaunchKernelGGL(k_batch_zsum<false>, dim3(bp.count), dim3(kZThreads), 0, s, bp.descs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (bp.n_heavy > 0) {
-    const unsigned hb = blocks_for(bp.n_heavy, kWavesPerBlock);
-    if (split)
-      hipLaunchKernelGGL(k_batch_attract_heavy<true>, dim3(hb), dim3(kBlock), 0, s, bp.descs, bp.heavy, bp.n_heavy);
-    else
-      hipLaunchKernelGGL(k_batch_attract_heavy<false>, dim3(hb), dim3(kBlock), 0, s, bp.descs, bp.heavy, bp.n_heavy);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (split)
-    hipLaunchKernelGGL(k_batch_update<true>, dim3(bp.n_row_blocks), dim3(kBlock), 0, s, bp.descs, bp.row_blocks, bp.T,
+  const dim3 rows(bp.n_row_blocks);
+  if (split && own_z)
+    hipLaunchKernelGGL((k_batch_update<true, true>), rows, dim3(kBlock), 0, s, bp.descs, bp.row_blocks, bp.T,
+                       p.early_exaggeration, p.exaggeration_iters, p.momentum_early, p.momentum_late, p.min_gain);
+  else if (split)
+    hipLaunchKernelGGL((k_batch_update<true, false>), rows, dim3(kBlock), 0, s, bp.descs, bp.row_blocks, bp.T,
+                       p.early_exaggeration, p.exaggeration_iters, p.momentum_early, p.momentum_late, p.min_gain);
+  else if (own_z)
+    hipLaunchKernelGGL((k_batch_update<false, true>), rows, dim3(kBlock), 0, s, bp.descs, bp.row_blocks, bp.T,
                        p.early_exaggeration, p.exaggeration_iters, p.momentum_early, p.momentum_late, p.min_gain);
   else
-    hipLaunchKernelGGL(k_batch_update<false>, dim3(bp.n_row_blocks), dim3(kBlock), 0, s, bp.descs, bp.row_blocks,
-                       bp.T, p.early_exaggeration, p.exaggeration_iters, p.momentum_early, p.momentum_late,
-                       p.min_gain);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_batch_advance, dim3(blocks_for(bp.count, kBlock)), dim3(kBlock), 0, s, bp.descs, bp.count);
+    hipLaunchKernelGGL((k_batch_update<false, false>), rows, dim3(kBlock), 0, s, bp.descs, bp.row_blocks, bp.T,
+                       p.early_exaggeration, p.exaggeration_iters, p.momentum_early, p.momentum_late, p.min_gain);
+  return hipGetLastError();
+}
+
+hipError_t launch_run_init(float2* U, float2* gains, int32_t n, int32_t* tstep, uint32_t* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_run_init, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, U, gains, n, tstep, flag);
   return hipGetLastError();
 }
 
