@@ -20,7 +20,8 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kFinal = 1024;          // threads of the one-block kernels
 constexpr int kMaxClusters = 1024;    // k-means centres held in LDS
-constexpr int kIterChunk = 8;         // k-means passes queued between checks
+constexpr int kIterChunk = 8;         // k-means passes queued before the first check
+constexpr int kMaxIterChunk = 32;     // and at most before a later one
 constexpr int kLdsContingency = 4096; // contingency tables up to this size are counted in LDS first
 constexpr uint32_t kErrFinite = 1u, kErrSeed = 2u, kErrLabel = 4u;
 
@@ -128,89 +129,133 @@ __global__ __launch_bounds__(kBlock) void k_km_init(const int2* __restrict__ q, 
   if (i < n) labels[i] = -1;
 }
 
-struct KmState {
-  double2* centre;          // [k]
-  unsigned long long* sum;  // [k][2] exact integer sums of the members
+// State of the passes (p = 1, 2, ...).  No launch reads what it writes: pass p
+// reads the totals as of pass p - 2 and what pass p - 1 added to them, writes
+// the totals as of pass p - 1 for the next pass, adds to its own `add` and
+// clears the next one's.
+struct KmTotals {
+  unsigned long long* sum;  // [k][2] exact integer sums of the members (modulo 2^64)
   int32_t* count;           // [k]
-  int32_t* changed;         // [blocks] labels changed per block in this pass
+};
+struct KmState {
+  double2* centre[2];       // [k] by p mod 2
+  KmTotals total[2];        // by p mod 2
+  KmTotals add[3];          // by p mod 3
+  int32_t* moved;           // [3] labels changed, by p mod 3
   int32_t* done;            // [0] converged, [1] passes made when converged
 };
 
-// One assignment pass: nearest centre (squared distance in FP64, no
-// contraction, ties to the lower index), per-block change count, and the
-// members' exact integer sums added to the cluster totals.
-__global__ __launch_bounds__(kBlock) void k_km_assign(const int2* __restrict__ q, int32_t n, int32_t k,
-                                                      int32_t* __restrict__ labels, KmState st) {
-  __shared__ double2 s_c[kMaxClusters];
-  __shared__ unsigned long long s_sum[2 * kMaxClusters];
-  __shared__ int32_t s_cnt[kMaxClusters];
-  if (st.done[0]) return;  // converged in an earlier pass of this chunk (uniform)
-  for (int c = threadIdx.x; c < k; c += kBlock) {
-    s_c[c] = st.centre[c];
+constexpr int kPassThreads = 1024;
+constexpr int kPointLanes = 4;                            // lanes that share a point's centres
+constexpr int kPassPoints = kPassThreads / kPointLanes;   // points per workgroup
+
+constexpr size_t km_lds_bytes(int32_t k) {
+  return (size_t)k * (sizeof(double2) + 2 * sizeof(unsigned long long) + sizeof(int32_t));
+}
+
+// Pass p.  Every workgroup moves the centres for itself (each non-empty
+// cluster's to its mean, an empty one's stays), assigns its points to the
+// nearest (squared distance in FP64, no contraction, ties to the lower index),
+// and the points that changed their cluster change the clusters' exact integer
+// sums and counts, in LDS and from there with device atomics.  A pass after
+// one that changed no label does nothing but pass that on.
+//
+// Latency is all there is to it (50 centres for 100,000 points are 1.3 us of
+// FP64).  Four lanes share a point's centres, and there is one launch a pass;
+// with one lane, all sums rebuilt in every pass (391 workgroups' atomics on
+// each cluster's address, which follow each other at 9 ns) and the centres
+// moved by a launch of their own, a pass took 20 + 4.5 us.  Leaving them to
+// the last workgroup to finish instead took 90 us: its fences write back L2.
+__global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict__ q, int32_t n, int32_t k, int32_t p,
+                                                          int32_t* __restrict__ labels, KmState st) {
+  extern __shared__ double2 s_c[];
+  unsigned long long* s_sum = reinterpret_cast<unsigned long long*>(s_c + k);
+  int32_t* s_cnt = reinterpret_cast<int32_t*>(s_sum + 2 * k);
+  const bool keeper = blockIdx.x == 0;  // the workgroup that writes the state
+  if (keeper && threadIdx.x == 0) st.moved[(p + 1) % 3] = 0;
+  if (p > 1 && st.moved[(p - 1) % 3] == 0) {  // converged (uniform)
+    if (keeper && threadIdx.x == 0 && st.done[0] == 0) {
+      st.done[0] = 1;
+      st.done[1] = p - 1;
+    }
+    return;
+  }
+  const KmTotals& total = st.total[(p - 1) & 1];
+  const KmTotals& added = st.add[(p - 1) % 3];
+  for (int c = threadIdx.x; c < k; c += kPassThreads) {
+    const unsigned long long x = total.sum[2 * c] + added.sum[2 * c];
+    const unsigned long long y = total.sum[2 * c + 1] + added.sum[2 * c + 1];
+    const int32_t count = total.count[c] + added.count[c];
+    double2 m = st.centre[(p - 1) & 1][c];
+    if (count > 0) m = make_double2((double)x / (double)count, (double)y / (double)count);
+    s_c[c] = m;
     s_sum[2 * c] = 0;
     s_sum[2 * c + 1] = 0;
     s_cnt[c] = 0;
+    if (keeper) {
+      const KmTotals& out = st.total[p & 1];
+      const KmTotals& next = st.add[(p + 1) % 3];
+      st.centre[p & 1][c] = m;
+      out.sum[2 * c] = x;
+      out.sum[2 * c + 1] = y;
+      out.count[c] = count;
+      next.sum[2 * c] = 0;
+      next.sum[2 * c + 1] = 0;
+      next.count[c] = 0;
+    }
   }
   __syncthreads();
-  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
+  const int sub = threadIdx.x & (kPointLanes - 1);
+  const int64_t i = (int64_t)blockIdx.x * kPassPoints + threadIdx.x / kPointLanes;
   bool moved = false;
   if (i < n) {
 #pragma clang fp contract(off)
-    const int2 p = q[i];
-    const double px = (double)p.x, py = (double)p.y;
+    const int2 pt = q[i];
+    const double px = (double)pt.x, py = (double)pt.y;
     int32_t best = 0;
     double bd = INFINITY;
-    for (int32_t c = 0; c < k; ++c) {
-      const double dx = px - s_c[c].x, dy = py - s_c[c].y;
+    for (int32_t c = sub; c < k; c += kPointLanes) {
+      const double2 m = s_c[c];
+      const double dx = px - m.x, dy = py - m.y;
       const double dist = dx * dx + dy * dy;
       if (dist < bd) {
         bd = dist;
         best = c;
       }
     }
-    moved = labels[i] != best;
-    labels[i] = best;
-    atomicAdd(&s_sum[2 * best], (unsigned long long)p.x);
-    atomicAdd(&s_sum[2 * best + 1], (unsigned long long)p.y);
-    atomicAdd(&s_cnt[best], 1);
+    for (int off = kPointLanes / 2; off > 0; off >>= 1) {
+      const double d2 = __shfl_xor(bd, off, kPointLanes);
+      const int32_t c2 = __shfl_xor(best, off, kPointLanes);
+      if (d2 < bd || (d2 == bd && c2 < best)) {
+        bd = d2;
+        best = c2;
+      }
+    }
+    if (sub == 0) {
+      const int32_t old = labels[i];
+      moved = old != best;
+      if (moved) {
+        labels[i] = best;
+        atomicAdd(&s_sum[2 * best], (unsigned long long)pt.x);
+        atomicAdd(&s_sum[2 * best + 1], (unsigned long long)pt.y);
+        atomicAdd(&s_cnt[best], 1);
+        if (old >= 0) {
+          atomicAdd(&s_sum[2 * old], 0ull - (unsigned long long)pt.x);
+          atomicAdd(&s_sum[2 * old + 1], 0ull - (unsigned long long)pt.y);
+          atomicAdd(&s_cnt[old], -1);
+        }
+      }
+    }
   }
   const int n_moved = __syncthreads_count(moved);
-  if (threadIdx.x == 0) st.changed[blockIdx.x] = n_moved;
-  for (int c = threadIdx.x; c < k; c += kBlock) {
-    if (s_cnt[c] > 0) {
-      atomicAdd(&st.sum[2 * c], s_sum[2 * c]);
-      atomicAdd(&st.sum[2 * c + 1], s_sum[2 * c + 1]);
-      atomicAdd(&st.count[c], s_cnt[c]);
-    }
+  if (n_moved == 0) return;
+  const KmTotals& mine = st.add[p % 3];
+  for (int c = threadIdx.x; c < k; c += kPassThreads) {
+    if (s_sum[2 * c]) atomicAdd(&mine.sum[2 * c], s_sum[2 * c]);
+    if (s_sum[2 * c + 1]) atomicAdd(&mine.sum[2 * c + 1], s_sum[2 * c + 1]);
+    if (s_cnt[c]) atomicAdd(&mine.count[c], s_cnt[c]);
   }
-}
-
-// One block: if no label changed in the pass, mark convergence (and the pass
-// number); otherwise move each non-empty cluster's centre to its mean.  The
-// sums are cleared for the next pass either way.
-__global__ __launch_bounds__(kFinal) void k_km_update(int32_t k, int32_t blocks, int32_t pass, KmState st) {
-  __shared__ int32_t s_tot[kFinal / kWave];
-  if (st.done[0]) return;
-  int32_t moved = 0;
-  for (int32_t b = threadIdx.x; b < blocks; b += kFinal) moved += st.changed[b];
-  for (int off = kWave / 2; off > 0; off >>= 1) moved += __shfl_xor(moved, off, kWave);
-  if ((threadIdx.x & (kWave - 1)) == 0) s_tot[threadIdx.x >> 6] = moved;
-  __syncthreads();
-  int32_t total = 0;
-  for (int w = 0; w < kFinal / kWave; ++w) total += s_tot[w];
-  for (int c = threadIdx.x; c < k; c += kFinal) {
-    if (total > 0 && st.count[c] > 0) {
-      const double cnt = (double)st.count[c];
-      st.centre[c] = make_double2((double)st.sum[2 * c] / cnt, (double)st.sum[2 * c + 1] / cnt);
-    }
-    st.sum[2 * c] = 0;
-    st.sum[2 * c + 1] = 0;
-    st.count[c] = 0;
-  }
-  if (threadIdx.x == 0 && total == 0) {
-    st.done[0] = 1;
-    st.done[1] = pass;
-  }
+  if (threadIdx.x == 0) atomicAdd(&st.moved[p % 3], n_moved);
 }
 
 // ---- NMI ----------------------------------------------------------------------
@@ -363,7 +408,7 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
   if (!Y_d || !seeds_d || !labels_d) return fail(TSGNE_E_INVAL, "null pointer");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const unsigned blocks = blocks_of(n);
-  // scratch: err + done | box | box partials | q | centres | sums | counts | changed
+  // scratch: err + done | box | box partials | q | moved | centres | totals and what passes add to them
   size_t o = 0;
   const size_t o_err = o;
   o = align256(o + 4 * sizeof(int32_t));
@@ -373,14 +418,14 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
   o = align256(o + sizeof(float4) * blocks);
   const size_t o_q = o;
   o = align256(o + sizeof(int2) * (size_t)n);
-  const size_t o_c = o;
-  o = align256(o + sizeof(double2) * (size_t)k);
-  const size_t o_sum = o;
-  o = align256(o + 2 * sizeof(unsigned long long) * (size_t)k);
-  const size_t o_cnt = o;
-  o = align256(o + sizeof(int32_t) * (size_t)k);
-  const size_t o_chg = o;
-  o = align256(o + sizeof(int32_t) * blocks);
+  const size_t o_zero = o;  // the rest starts as 0
+  const size_t o_moved = o;
+  o = align256(o + 3 * sizeof(int32_t));
+  const size_t o_c[2] = {o, o + align256(sizeof(double2) * (size_t)k)};
+  o += 2 * align256(sizeof(double2) * (size_t)k);
+  const size_t b_sum = align256(2 * sizeof(unsigned long long) * (size_t)k), b_cnt = align256(sizeof(int32_t) * (size_t)k);
+  const size_t o_tot = o;
+  o += 5 * (b_sum + b_cnt);
   ScratchBlock tmp;
   tmp.s = s;
   TSGNE_HIP(scratch_alloc(&tmp.p, o, s), "allocate k-means state");
@@ -388,15 +433,22 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
   uint32_t* const err = reinterpret_cast<uint32_t*>(base + o_err);
   int32_t* const done = reinterpret_cast<int32_t*>(base + o_err) + 2;
   double* const box = reinterpret_cast<double*>(base + o_box);
-  KmState st{reinterpret_cast<double2*>(base + o_c), reinterpret_cast<unsigned long long*>(base + o_sum),
-             reinterpret_cast<int32_t*>(base + o_cnt), reinterpret_cast<int32_t*>(base + o_chg), done};
+  KmState st;
+  for (int b = 0; b < 2; ++b) st.centre[b] = reinterpret_cast<double2*>(base + o_c[b]);
+  for (int b = 0; b < 5; ++b) {
+    char* const at = base + o_tot + (size_t)b * (b_sum + b_cnt);
+    (b < 2 ? st.total[b] : st.add[b - 2]) =
+        KmTotals{reinterpret_cast<unsigned long long*>(at), reinterpret_cast<int32_t*>(at + b_sum)};
+  }
+  st.moved = reinterpret_cast<int32_t*>(base + o_moved);
+  st.done = done;
   TSGNE_HIP(hipMemsetAsync(base + o_err, 0, 4 * sizeof(int32_t), s), "clear flags");
-  TSGNE_HIP(hipMemsetAsync(base + o_sum, 0, o_chg - o_sum, s), "clear sums");
+  TSGNE_HIP(hipMemsetAsync(base + o_zero, 0, o - o_zero, s), "clear sums");
   const float2* Y = reinterpret_cast<const float2*>(Y_d);
   int2* const q = reinterpret_cast<int2*>(base + o_q);
   TSGNE_HIP(launch_box(Y, n, reinterpret_cast<float4*>(base + o_part), box, err, s), "launch layout box");
   hipLaunchKernelGGL(k_quantise, dim3(blocks), dim3(kBlock), 0, s, Y, n, box, q);
-  hipLaunchKernelGGL(k_km_init, dim3(blocks_of(std::max(n, k))), dim3(kBlock), 0, s, q, n, seeds_d, k, st.centre,
+  hipLaunchKernelGGL(k_km_init, dim3(blocks_of(std::max(n, k))), dim3(kBlock), 0, s, q, n, seeds_d, k, st.centre[0],
                      labels_d, err);
   TSGNE_HIP(hipGetLastError(), "launch k-means set-up");
   uint32_t host_err = 0;
@@ -406,13 +458,16 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
   if (host_err & kErrSeed) return fail(TSGNE_E_INVAL, "a seed index lies outside [0, n)");
 
   int32_t host_done[2] = {0, 0};
-  int32_t pass = 0;
+  int32_t pass = 0, chunk = kIterChunk;
+  const unsigned pass_blocks = (unsigned)(((int64_t)n + kPassPoints - 1) / kPassPoints);
   while (pass < max_iter) {
-    const int32_t last = std::min(max_iter, pass + kIterChunk);
-    for (int32_t it = pass + 1; it <= last; ++it) {
-      hipLaunchKernelGGL(k_km_assign, dim3(blocks), dim3(kBlock), 0, s, q, n, k, labels_d, st);
-      hipLaunchKernelGGL(k_km_update, dim3(1), dim3(kFinal), 0, s, k, (int32_t)blocks, it, st);
-    }
+    // a pass after convergence returns at once: later chunks are longer, as a
+    // check costs more than a few of those
+    const int32_t last = (int32_t)std::min<int64_t>(max_iter, (int64_t)pass + chunk);
+    chunk = std::min(2 * chunk, kMaxIterChunk);
+    for (int32_t it = pass + 1; it <= last; ++it)
+      hipLaunchKernelGGL(k_km_pass, dim3(pass_blocks), dim3(kPassThreads), km_lds_bytes(k), s, q, n, k, it, labels_d,
+                         st);
     TSGNE_HIP(hipGetLastError(), "launch k-means passes");
     TSGNE_HIP(hipMemcpyAsync(host_done, done, sizeof(host_done), hipMemcpyDeviceToHost, s), "read convergence");
     TSGNE_HIP(hipStreamSynchronize(s), "synchronise k-means passes");

@@ -109,3 +109,16 @@ def test_quality_rejects(gpu):
     with pytest.raises(tsgne.TsgneError) as e:
         tsgne.tsgne_nmi(lab, 1, bad, 3)
     assert e.value.status == tsgne.TSGNE_E_INVAL
+
+
+@pytest.mark.parametrize("n,k", [(1, 1), (255, 2), (256, 3), (257, 4), (511, 5), (8192, 7), (8193, 6), (8449, 64)])
+def test_kmeans_at_group_edges(gpu, n, k):
+    """Around the 256 points of a workgroup, the 4 lanes that share a point's
+    centres and the 32 groups its workgroups are counted in."""
+    import torch
+    Y, _ = blobs(n, min(k, 9), n, 6.0)
+    seeds = np.random.default_rng(n).choice(n, k, replace=False).astype(np.int32)
+    labels, iters = tsgne.tsgne_kmeans(torch.from_numpy(Y).to(gpu), torch.from_numpy(seeds).to(gpu))
+    ol, oit = oracle.kmeans(Y, seeds)
+    assert iters == oit
+    assert np.array_equal(labels.cpu().numpy(), ol)
