@@ -236,11 +236,9 @@ tsgne_status graph_structure(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
                              tsgne_graph** out);
 void free_graph(tsgne_graph* g);
 // Checks on the device that (row_ptr, col) is a canonical symmetric CSR
-// (synchronising; E_GRAPH otherwise).
-tsgne_status validate_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, hipStream_t s);
-// The same in caller-provided device scratch of validate_csr_bytes(n, nnz);
-// *row_of_out (nullable) then points at the row of every entry, inside the
-// scratch.
+// (synchronising; E_GRAPH otherwise), in caller-provided device scratch of
+// validate_csr_bytes(n, nnz); *row_of_out (nullable) then points at the row of
+// every entry, inside the scratch.
 size_t validate_csr_bytes(int32_t n, int64_t nnz);
 tsgne_status validate_csr_in(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, void* scratch,
                              hipStream_t s, int32_t** row_of_out = nullptr);

@@ -3,16 +3,22 @@
 // on G, nearest by breadth-first search.  The first k neighbours of i are the
 // k smallest nodes j != i under (hop distance from i, node id).
 //
-// One wave per source node.  Each BFS level is enumerated in ascending id
-// order by a wave-wide k-way merge of the frontier's adjacency rows (CSR rows
-// are sorted): every lane owns up to kPerLane frontier rows with a cursor, the
-// wave takes the minimum head, advances every cursor holding it (duplicates),
-// and keeps it if it is not yet visited.  The visited set and the frontier are
-// striped over the lanes' registers (membership is one ballot), so nothing is
-// shared through memory inside a wave.  The directed lists are then made
-// symmetric and canonical with a radix sort and a unique pass.
+// One wave per source node.  Level 1 is the source's own row.  Every further
+// level is enumerated in ascending id order by a wave-wide k-way merge of the
+// frontier's adjacency rows (CSR rows are sorted): every lane owns up to U
+// frontier rows with a cursor, the wave takes the minimum head, advances every
+// cursor holding it (duplicates), and keeps it if it is not yet visited.  The
+// visited set and the frontier are striped over the lanes' registers
+// (membership is one ballot), so nothing is shared through memory inside a
+// wave.  Each list leaves the kernel sorted by id.
+//
+// The lists are made symmetric by transposing them (a stable radix sort of
+// the pairs by their target, whose sources stay ascending) and merging every
+// node's list with its column of the transpose: an entry's place is its index
+// plus the number of smaller entries of the other list, less the pairs chosen
+// from both ends that come before it.
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_select.hpp>
+#include <rocprim/device/device_scan.hpp>
 
 #include <algorithm>
 #include <climits>
@@ -25,123 +31,214 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr int kPerLane = 4;                 // frontier rows per lane
-constexpr int kMaxK = kWave * kPerLane;     // 256
-constexpr int kVisPerLane = kPerLane + 1;   // visited: k + 1 entries
+constexpr int kMaxPerLane = 4;                 // frontier rows per lane
+constexpr int kMaxK = kWave * kMaxPerLane;     // 256
 
+// Minimum over the wave, to every lane: DPP row shifts and broadcasts leave it
+// in the last lane (a shuffle goes through LDS; six of them were most of a
+// merge step).
 __device__ __forceinline__ int32_t wave_min(int32_t v) {
-  for (int off = kWave / 2; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, kWave));
-  return v;
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x112, 0xF, 0xF, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x114, 0xF, 0xF, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x118, 0xF, 0xF, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+  v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+  return __builtin_amdgcn_readlane(v, kWave - 1);
 }
 
+// U = ceil(k / 64) rows and found nodes per lane.  Bound by instruction issue
+// (some hundred merge steps per node): 0.83 ms for k = 90 on 100,000 nodes
+// with shuffles and U = 4 for every k.
+template <int U>
 __global__ __launch_bounds__(kBlock) void k_knn_bfs(const int32_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ col, int32_t n, int32_t k,
                                                     int32_t* __restrict__ out, int32_t* __restrict__ out_count) {
   const int32_t i = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
   if (i >= n) return;
   const int lane = threadIdx.x & (kWave - 1);
-  int32_t vis[kVisPerLane];  // visited node at index lane + 64 u
-  int32_t fcur[kPerLane], fend[kPerLane], fhead[kPerLane];
-  int32_t nfront[kPerLane];  // the level being taken (next frontier)
+  int32_t hit[U];                          // node found at index lane + 64 u
+  int32_t fcur[U], fend[U], fhead[U];
+  int32_t nfront[U];                       // the level being taken (next frontier)
+  const int32_t b = row_ptr[i], deg = row_ptr[i + 1] - b;
+  int32_t found = min(deg, k), taken = found;
 #pragma unroll
-  for (int u = 0; u < kVisPerLane; ++u) vis[u] = -1;
-  if (lane == 0) vis[0] = i;
-  int32_t n_vis = 1;
-  // frontier = {i}, owned by lane 0
-#pragma unroll
-  for (int u = 0; u < kPerLane; ++u) {
-    fcur[u] = 0;
-    fend[u] = 0;
-    fhead[u] = INT_MAX;
+  for (int u = 0; u < U; ++u) {
+    const int t = u * kWave + lane;
+    hit[u] = t < found ? col[b + t] : -1;
+    nfront[u] = hit[u];
   }
-  if (lane == 0) {
-    fcur[0] = row_ptr[i];
-    fend[0] = row_ptr[i + 1];
-    fhead[0] = fcur[0] < fend[0] ? col[fcur[0]] : INT_MAX;
-  }
-  int32_t found = 0;
-  while (found < k) {
-    int32_t taken = 0;
-    for (;;) {
-      int32_t h = INT_MAX;
-#pragma unroll
-      for (int u = 0; u < kPerLane; ++u) h = min(h, fhead[u]);
-      const int32_t m = wave_min(h);
-      if (m == INT_MAX) break;  // level exhausted
-#pragma unroll
-      for (int u = 0; u < kPerLane; ++u) {
-        if (fhead[u] == m) {
-          ++fcur[u];
-          fhead[u] = fcur[u] < fend[u] ? col[fcur[u]] : INT_MAX;
-        }
-      }
-      bool mine = false;
-#pragma unroll
-      for (int u = 0; u < kVisPerLane; ++u) mine |= (vis[u] == m);
-      if (__ballot(mine) != 0) continue;  // visited (an earlier level or the source)
-      // take m: output, visited, next frontier (striped by index)
-      if (lane == 0) out[(int64_t)i * k + found] = m;
-#pragma unroll
-      for (int u = 0; u < kVisPerLane; ++u)
-        if (n_vis == u * kWave + lane) vis[u] = m;
-#pragma unroll
-      for (int u = 0; u < kPerLane; ++u)
-        if (taken == u * kWave + lane) nfront[u] = m;
-      ++n_vis;
-      ++taken;
-      ++found;
-      if (found == k) break;
-    }
-    if (taken == 0 || found == k) break;  // component exhausted, or done
+  while (taken > 0 && found < k) {
     // the level just taken becomes the frontier
 #pragma unroll
-    for (int u = 0; u < kPerLane; ++u) {
+    for (int u = 0; u < U; ++u) {
+      fcur[u] = fend[u] = 0;
+      fhead[u] = INT_MAX;
       if (u * kWave + lane < taken) {
         const int32_t v = nfront[u];
         fcur[u] = row_ptr[v];
         fend[u] = row_ptr[v + 1];
         fhead[u] = fcur[u] < fend[u] ? col[fcur[u]] : INT_MAX;
-      } else {
-        fcur[u] = fend[u] = 0;
-        fhead[u] = INT_MAX;
       }
     }
+    taken = 0;
+    for (;;) {
+      int32_t h = fhead[0];
+#pragma unroll
+      for (int u = 1; u < U; ++u) h = min(h, fhead[u]);
+      const int32_t m = wave_min(h);
+      if (m == INT_MAX) break;  // level exhausted
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (fhead[u] == m) {
+          ++fcur[u];
+          fhead[u] = fcur[u] < fend[u] ? col[fcur[u]] : INT_MAX;
+        }
+      }
+      if (m == i) continue;  // the source
+      bool mine = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) mine |= (hit[u] == m);
+      if (__ballot(mine) != 0) continue;  // visited on this or an earlier level
+      // take m: found and next frontier (striped by index)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (found == u * kWave + lane) hit[u] = m;
+        if (taken == u * kWave + lane) nfront[u] = m;
+      }
+      ++taken;
+      ++found;
+      if (found == k) break;
+    }
   }
+  // in order of id: every node's rank among the found
+  int32_t rank[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) rank[u] = 0;
+#pragma unroll
+  for (int v = 0; v < U; ++v) {
+    const int32_t count = min(kWave, found - v * kWave);
+    for (int32_t t = 0; t < count; ++t) {
+      const int32_t other = __builtin_amdgcn_readlane(hit[v], t);
+#pragma unroll
+      for (int u = 0; u < U; ++u) rank[u] += other < hit[u] ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u * kWave + lane < found) out[(int64_t)i * k + rank[u]] = hit[u];
   if (lane == 0) out_count[i] = found;
 }
 
-// Both directions of every chosen pair as (row << 32 | col); empty slots get
-// the largest key, which sorts last.
-__global__ __launch_bounds__(kBlock) void k_knn_keys(const int32_t* __restrict__ out,
-                                                     const int32_t* __restrict__ count, int32_t n, int32_t k,
-                                                     uint64_t* __restrict__ keys) {
-  const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (s >= (int64_t)n * k) return;
-  const int32_t i = (int32_t)(s / k), t = (int32_t)(s - (int64_t)i * k);
-  uint64_t a = ~0ull, b = ~0ull;
-  if (t < count[i]) {
-    const uint64_t j = (uint32_t)out[s];
-    a = ((uint64_t)(uint32_t)i << 32) | j;
-    b = (j << 32) | (uint32_t)i;
-  }
-  keys[2 * s] = a;
-  keys[2 * s + 1] = b;
+// The chosen pairs by target and source; empty slots get the target n, which
+// sorts last.
+__global__ __launch_bounds__(kBlock) void k_knn_pairs(const int32_t* __restrict__ out,
+                                                      const int32_t* __restrict__ count, int32_t n, int32_t k,
+                                                      uint32_t* __restrict__ target, int32_t* __restrict__ source) {
+  const uint32_t t = blockIdx.x * kBlock + threadIdx.x;  // n * k < 2^30
+  if (t >= (uint32_t)n * (uint32_t)k) return;
+  const int32_t i = (int32_t)(t / (uint32_t)k);
+  target[t] = (int32_t)(t - (uint32_t)i * (uint32_t)k) < count[i] ? (uint32_t)out[t] : (uint32_t)n;
+  source[t] = i;
 }
 
-__global__ __launch_bounds__(kBlock) void k_knn_csr(const uint64_t* __restrict__ keys, int64_t nnz, int32_t n,
-                                                    int32_t* __restrict__ row_ptr, int32_t* __restrict__ col) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t < nnz) col[t] = (int32_t)(keys[t] & 0xffffffffull);
-  if (t <= n) {
-    // first entry whose row is >= t
-    int64_t lo = 0, hi = nnz;
-    const uint64_t target = (uint64_t)t << 32;
-    while (lo < hi) {
-      const int64_t mid = lo + (hi - lo) / 2;
-      if (keys[mid] < target) lo = mid + 1; else hi = mid;
-    }
-    row_ptr[t] = (int32_t)lo;
+// First index in sorted[lo, hi) whose value is not below x.
+template <typename V>
+__device__ __forceinline__ int64_t lower_bound_of(const V* __restrict__ sorted, int64_t lo, int64_t hi, V x) {
+  while (lo < hi) {
+    const int64_t mid = lo + (hi - lo) / 2;
+    if (sorted[mid] < x) lo = mid + 1;
+    else hi = mid;
   }
+  return lo;
+}
+
+// in_ptr[j] = first pair of target j, j <= n.
+__global__ __launch_bounds__(kBlock) void k_knn_in_ptr(const uint32_t* __restrict__ target, int64_t slots, int32_t n,
+                                                       int32_t* __restrict__ in_ptr) {
+  const int32_t j = blockIdx.x * kBlock + threadIdx.x;
+  if (j <= n) in_ptr[j] = (int32_t)lower_bound_of<uint32_t>(target, 0, slots, (uint32_t)j);
+}
+
+// One wave per node j, its list out[0, m) against the sorted sources that chose
+// j: before[t] = sources below out[t] less the pairs chosen from both ends
+// among out[0, t), both[t] = those pairs (both[m] all of them), size = the
+// length of the union.
+template <int U>
+__global__ __launch_bounds__(kBlock) void k_knn_overlap(const int32_t* __restrict__ out,
+                                                        const int32_t* __restrict__ count,
+                                                        const int32_t* __restrict__ in_ptr,
+                                                        const int32_t* __restrict__ source, int32_t n, int32_t k,
+                                                        int32_t* __restrict__ before, int32_t* __restrict__ both,
+                                                        int32_t* __restrict__ size) {
+  const int32_t j = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
+  if (j > n) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  if (j == n) {  // one more entry, so that a scan of the sizes ends with their sum
+    if (lane == 0) size[n] = 0;
+    return;
+  }
+  const int32_t m = count[j];
+  const int64_t lo = in_ptr[j], hi = in_ptr[j + 1];
+  int32_t shared = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = u * kWave + lane;
+    bool dup = false;
+    int64_t at = lo;
+    if (t < m) {
+      const int32_t x = out[(int64_t)j * k + t];
+      at = lower_bound_of<int32_t>(source, lo, hi, x);
+      dup = at < hi && source[at] == x;
+    }
+    const unsigned long long mask = __ballot(dup);
+    const int32_t ahead = shared + __popcll(mask & ((1ull << lane) - 1));
+    if (t < m) {
+      before[(int64_t)j * k + t] = (int32_t)(at - lo) - ahead;
+      both[(int64_t)j * (k + 1) + t] = ahead;
+    }
+    shared += __popcll(mask);
+  }
+  if (lane == 0) {
+    both[(int64_t)j * (k + 1) + m] = shared;
+    size[j] = m + (int32_t)(hi - lo) - shared;
+  }
+}
+
+// Entry t of the lists and pair t of the transpose into their places.
+__global__ __launch_bounds__(kBlock) void k_knn_merge(const int32_t* __restrict__ out,
+                                                      const int32_t* __restrict__ count,
+                                                      const int32_t* __restrict__ before,
+                                                      const int32_t* __restrict__ both,
+                                                      const uint32_t* __restrict__ target,
+                                                      const int32_t* __restrict__ source,
+                                                      const int32_t* __restrict__ in_ptr, int32_t n, int32_t k,
+                                                      const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col) {
+  const uint32_t t = blockIdx.x * kBlock + threadIdx.x;  // n * k < 2^30
+  if (t >= (uint32_t)n * (uint32_t)k) return;
+  const int32_t i = (int32_t)(t / (uint32_t)k), at = (int32_t)(t - (uint32_t)i * (uint32_t)k);
+  if (at < count[i]) col[row_ptr[i] + at + before[t]] = out[t];
+  const int32_t j = (int32_t)target[t];
+  if (j == n) return;
+  const int32_t x = source[t], m = count[j];
+  const int32_t* __restrict__ list = out + (int64_t)j * k;
+  const int32_t below = (int32_t)lower_bound_of<int32_t>(list, 0, m, x);
+  if (below < m && list[below] == x) return;  // chosen from both ends: the list has it
+  col[row_ptr[j] + ((int32_t)t - in_ptr[j]) - both[(int64_t)j * (k + 1) + below] + below] = x;
+}
+
+template <int U>
+void launch_lists(const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t k, int32_t* out, int32_t* count,
+                  hipStream_t s) {
+  hipLaunchKernelGGL(k_knn_bfs<U>, dim3((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0, s,
+                     row_ptr, col, n, k, out, count);
+}
+
+template <int U>
+void launch_overlap(const int32_t* out, const int32_t* count, const int32_t* in_ptr, const int32_t* source, int32_t n,
+                    int32_t k, int32_t* before, int32_t* both, int32_t* size, hipStream_t s) {
+  hipLaunchKernelGGL(k_knn_overlap<U>, dim3((unsigned)((n + 1 + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
+                     0, s, out, count, in_ptr, source, n, k, before, both, size);
 }
 
 unsigned blocks_for(int64_t work) { return (unsigned)((work + kBlock - 1) / kBlock); }
@@ -150,13 +247,6 @@ unsigned blocks_for(int64_t work) { return (unsigned)((work + kBlock - 1) / kBlo
 
 size_t validate_csr_bytes(int32_t n, int64_t nnz) {
   return sizeof(int32_t) * (4 + 2 * (size_t)row_check_blocks(n) + 2 * (size_t)nnz);
-}
-
-tsgne_status validate_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, hipStream_t s) {
-  ScratchBlock tmp;
-  tmp.s = s;
-  TSGNE_HIP(scratch_alloc(&tmp.p, validate_csr_bytes(n, nnz), s), "allocate CSR check buffers");
-  return validate_csr_in(n, nnz, row_ptr, col, tmp.p, s);
 }
 
 // Checks that (row_ptr, col) is a canonical symmetric CSR, in scratch of
@@ -203,62 +293,74 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
     return fail(TSGNE_E_INVAL, "null pointer");
   if ((int64_t)n * k * 2 >= ((int64_t)1 << 31)) return fail(TSGNE_E_INVAL, "n * k too large");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (tsgne_status st = validate_csr(n, nnz, row_ptr_d, col_d, s)) return st;
-
   const int64_t slots = (int64_t)n * k;
-  int32_t* out = nullptr;
-  int32_t* count = nullptr;
-  uint64_t* keys = nullptr;
-  uint64_t* sorted = nullptr;
-  int64_t* n_unique = nullptr;
-  void* temp = nullptr;
-  struct Tmp {
-    int32_t*& o;
-    int32_t*& c;
-    uint64_t*& k1;
-    uint64_t*& k2;
-    int64_t*& u;
-    void*& t;
-    ~Tmp() {
-      dfree(o);
-      dfree(c);
-      dfree(k1);
-      dfree(k2);
-      dfree(u);
-      if (t) (void)hipFree(t);
-    }
-  } tmp{out, count, keys, sorted, n_unique, temp};
-  TSGNE_HIP(dalloc(&out, (size_t)slots), "allocate neighbour lists");
-  TSGNE_HIP(dalloc(&count, (size_t)n), "allocate counts");
-  TSGNE_HIP(dalloc(&keys, 2 * (size_t)slots), "allocate keys");
-  TSGNE_HIP(dalloc(&sorted, 2 * (size_t)slots), "allocate keys");
-  TSGNE_HIP(dalloc(&n_unique, 1), "allocate count");
+  int bits = 1;  // targets 0 .. n
+  while (((int64_t)1 << bits) <= n) ++bits;
+  size_t sort_bytes = 0, scan_bytes = 0;
+  TSGNE_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, (uint32_t*)nullptr, (uint32_t*)nullptr, (int32_t*)nullptr,
+                                      (int32_t*)nullptr, (size_t)slots, 0, bits, s), "size sort");
+  TSGNE_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, (int32_t*)nullptr, (int32_t*)nullptr, 0, (size_t)n + 1,
+                                    rocprim::plus<int32_t>(), s), "size scan");
+  // scratch: lists | counts | in_ptr | sizes | pairs before and after the sort
+  // (the unsorted ones' place is taken by before and both) | rocPRIM's own;
+  // the CSR check, which is done before any of them, from the same start.  One
+  // allocation: with a second, small one before it the pool now and then gave
+  // that one the large block and took 5 ms to make room for the other.
+  size_t o = 0;
+  auto place = [&](size_t bytes) {
+    const size_t at = o;
+    o += (bytes + 255) & ~(size_t)255;
+    return at;
+  };
+  const size_t o_out = place(sizeof(int32_t) * (size_t)slots);
+  const size_t o_count = place(sizeof(int32_t) * (size_t)n);
+  const size_t o_in = place(sizeof(int32_t) * ((size_t)n + 1));
+  const size_t o_size = place(sizeof(int32_t) * ((size_t)n + 1));
+  const size_t o_t0 = place(sizeof(int32_t) * (size_t)slots);
+  const size_t o_s0 = place(sizeof(int32_t) * ((size_t)slots + (size_t)n));
+  const size_t o_t1 = place(sizeof(int32_t) * (size_t)slots);
+  const size_t o_s1 = place(sizeof(int32_t) * (size_t)slots);
+  const size_t o_temp = place(std::max<size_t>(std::max(sort_bytes, scan_bytes), 1));
+  ScratchBlock tmp;
+  tmp.s = s;
+  TSGNE_HIP(scratch_alloc(&tmp.p, std::max(o, validate_csr_bytes(n, nnz)), s), "allocate neighbour lists");
+  char* const base = static_cast<char*>(tmp.p);
+  if (tsgne_status st = validate_csr_in(n, nnz, row_ptr_d, col_d, base, s)) return st;
+  auto ints = [&](size_t at) { return reinterpret_cast<int32_t*>(base + at); };
+  int32_t *out = ints(o_out), *count = ints(o_count), *in_ptr = ints(o_in), *size = ints(o_size);
+  uint32_t *t0 = reinterpret_cast<uint32_t*>(base + o_t0), *t1 = reinterpret_cast<uint32_t*>(base + o_t1);
+  int32_t *s0 = ints(o_s0), *s1 = ints(o_s1), *before = ints(o_t0), *both = ints(o_s0);
+  void* const temp = base + o_temp;
 
-  hipLaunchKernelGGL(k_knn_bfs, dim3((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0, s,
-                     row_ptr_d, col_d, n, k, out, count);
+  switch ((k + kWave - 1) / kWave) {
+    case 1: launch_lists<1>(row_ptr_d, col_d, n, k, out, count, s); break;
+    case 2: launch_lists<2>(row_ptr_d, col_d, n, k, out, count, s); break;
+    case 3: launch_lists<3>(row_ptr_d, col_d, n, k, out, count, s); break;
+    default: launch_lists<4>(row_ptr_d, col_d, n, k, out, count, s); break;
+  }
   TSGNE_HIP(hipGetLastError(), "launch BFS");
-  hipLaunchKernelGGL(k_knn_keys, dim3(blocks_for(slots)), dim3(kBlock), 0, s, out, count, n, k, keys);
-  TSGNE_HIP(hipGetLastError(), "launch key build");
-  // keys below 2^(32 + bits(n)) except the sentinel; sort all 64 bits
-  size_t sort_bytes = 0, uniq_bytes = 0;
-  const int n_keys = (int)(2 * slots);
-  TSGNE_HIP(rocprim::radix_sort_keys(nullptr, sort_bytes, keys, sorted, n_keys, 0, 64, s), "size sort");
-  TSGNE_HIP(rocprim::unique(nullptr, uniq_bytes, sorted, keys, n_unique, (size_t)n_keys, rocprim::equal_to<uint64_t>(), s), "size unique");
-  TSGNE_HIP(hipMalloc(&temp, std::max<size_t>(std::max(sort_bytes, uniq_bytes), 1)), "allocate sort scratch");
-  TSGNE_HIP(rocprim::radix_sort_keys(temp, sort_bytes, keys, sorted, n_keys, 0, 64, s), "sort keys");
-  TSGNE_HIP(rocprim::unique(temp, uniq_bytes, sorted, keys, n_unique, (size_t)n_keys, rocprim::equal_to<uint64_t>(), s), "unique keys");
-  int64_t host_unique = 0;
-  TSGNE_HIP(hipMemcpyAsync(&host_unique, n_unique, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read count");
-  TSGNE_HIP(hipStreamSynchronize(s), "synchronise unique");
-  uint64_t last = 0;
-  if (host_unique > 0)
-    TSGNE_HIP(hipMemcpy(&last, keys + host_unique - 1, sizeof(uint64_t), hipMemcpyDeviceToHost), "read last key");
-  const int64_t total = host_unique - ((host_unique > 0 && last == ~0ull) ? 1 : 0);
+  hipLaunchKernelGGL(k_knn_pairs, dim3(blocks_for(slots)), dim3(kBlock), 0, s, out, count, n, k, t0, s0);
+  TSGNE_HIP(hipGetLastError(), "launch pairs");
+  TSGNE_HIP(rocprim::radix_sort_pairs(temp, sort_bytes, t0, t1, s0, s1, (size_t)slots, 0, bits, s), "sort pairs");
+  hipLaunchKernelGGL(k_knn_in_ptr, dim3(blocks_for((int64_t)n + 1)), dim3(kBlock), 0, s, t1, slots, n, in_ptr);
+  TSGNE_HIP(hipGetLastError(), "launch transpose");
+  switch ((k + kWave - 1) / kWave) {
+    case 1: launch_overlap<1>(out, count, in_ptr, s1, n, k, before, both, size, s); break;
+    case 2: launch_overlap<2>(out, count, in_ptr, s1, n, k, before, both, size, s); break;
+    case 3: launch_overlap<3>(out, count, in_ptr, s1, n, k, before, both, size, s); break;
+    default: launch_overlap<4>(out, count, in_ptr, s1, n, k, before, both, size, s); break;
+  }
+  TSGNE_HIP(hipGetLastError(), "launch overlap");
+  TSGNE_HIP(rocprim::exclusive_scan(temp, scan_bytes, size, knn_row_ptr_d, 0, (size_t)n + 1, rocprim::plus<int32_t>(),
+                                    s), "scan row sizes");
+  int32_t total = 0;
+  TSGNE_HIP(hipMemcpyAsync(&total, knn_row_ptr_d + n, sizeof(int32_t), hipMemcpyDeviceToHost, s), "read size");
+  TSGNE_HIP(hipStreamSynchronize(s), "synchronise row sizes");
   *knn_nnz = total;
   if (total > knn_capacity) return fail(TSGNE_E_INVAL, "knn_col capacity is smaller than the result (see *knn_nnz)");
-  hipLaunchKernelGGL(k_knn_csr, dim3(blocks_for(std::max<int64_t>(total, (int64_t)n + 1))), dim3(kBlock), 0, s, keys,
-                     total, n, knn_row_ptr_d, knn_col_d);
-  TSGNE_HIP(hipGetLastError(), "launch CSR build");
+  hipLaunchKernelGGL(k_knn_merge, dim3(blocks_for(slots)), dim3(kBlock), 0, s, out, count, before, both, t1, s1,
+                     in_ptr, n, k, knn_row_ptr_d, knn_col_d);
+  TSGNE_HIP(hipGetLastError(), "launch merge");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise kNN graph");
   return TSGNE_OK;
 }

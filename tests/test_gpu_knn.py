@@ -69,3 +69,20 @@ def test_knn_graph_rejects(gpu):
     with pytest.raises(tsgne.TsgneError) as e:
         tsgne.tsgne_knn_graph(d_rp, torch.from_numpy(bad).to(gpu), 5)
     assert e.value.status == tsgne.TSGNE_E_GRAPH
+
+
+@pytest.mark.parametrize("k", [1, 2, 63, 64, 65, 127, 128, 129, 192, 193, 256])
+def test_knn_graph_at_register_edges(gpu, k):
+    """Lists around the 64 lanes of a wave and their registers: a star (one
+    node in every list), a clique larger than k, a path, a pair and isolated
+    nodes."""
+    import torch
+    edges = [(0, i) for i in range(1, 400)]
+    edges += [(i, j) for i in range(400, 670) for j in range(i + 1, 670)]
+    edges += [(i, i + 1) for i in range(670, 1000)] + [(1000, 1001)]
+    n = 1005
+    rp, col = tsgne.tsgne_csr_from_edges(n, edges)
+    krp, kcol = tsgne.tsgne_knn_graph(torch.from_numpy(rp).to(gpu), torch.from_numpy(col).to(gpu), k)
+    orp, ocol = oracle.knn_graph(rp, col, k)
+    assert np.array_equal(krp.cpu().numpy(), orp)
+    assert np.array_equal(kcol.cpu().numpy(), ocol)
