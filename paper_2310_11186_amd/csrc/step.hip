@@ -243,6 +243,95 @@ __device__ __forceinline__ void tile_symmetric(const float2* __restrict__ Y, int
   }
 }
 
+// Waves that share a symmetric tile, each with one of its R passes: tiles of 2
+// and 4 rows are those of graphs that leave the chip short of waves, where a
+// step waits for one wave's tile (9,001 nodes, 2 rows: 2.4 tiles per SIMD).
+template <int R>
+constexpr int tile_waves() {
+  return R == 2 || R == 4 ? R : 1;
+}
+// The same for the host, and tiles per workgroup.
+__host__ __device__ __forceinline__ int tiles_per_block(int R) {
+  return kWavesPerBlock / (R == 2 || R == 4 ? R : 1);
+}
+
+// LDS of the waves that share a tile.
+template <int R>
+struct SharedTile {
+  reg_pair rows[R][R][kWave];  // [pass][row] sums of the resident rows
+  double z[R][kWave];          // [pass] Z terms
+};
+
+// A symmetric tile by R waves: wave q of them takes pass q, and the sums of
+// the resident rows and of Z are added in pass order through LDS, so the
+// forces are bitwise those of the passes one after the other.  Every wave of
+// the workgroup calls this (live = false without a tile).
+template <int R, bool SPLIT, bool FORCES = true>
+__device__ __forceinline__ void tile_symmetric_shared(const float2* __restrict__ Y, int32_t n, int32_t nb, int32_t a,
+                                                      int32_t b, float2* __restrict__ part,
+                                                      double* __restrict__ zpart, float* __restrict__ zpart32,
+                                                      int64_t item, bool live, int q, int lane, float2* cols,
+                                                      SharedTile<R>& sh) {
+  constexpr int T = kWave * R;
+  constexpr int G = recip_group<R>();
+  if (live) {
+    const int32_t valid_b = min(T, n - b * T);
+    const int jl = q * kWave + lane;
+    const bool vj = jl < valid_b;
+    const float2 v = vj ? Y[(int64_t)b * T + jl] : make_float2(0.f, 0.f);
+    float2 y[R];
+    reg_pair res[R], tw[G];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      y[r] = Y[(int64_t)a * T + r * kWave + lane];
+      res[r] = reg_pair{0.f, 0.f};
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) tw[g] = reg_pair{0.f, 0.f};
+    double z64 = 0.0;
+    float z32 = 0.f;
+    float fx = 0.f, fy = 0.f;
+    cols[lane] = v;
+    cols[lane + kWave] = v;
+    wave_lds_fence();
+    const int valid = valid_b - q * kWave;
+    if (valid >= kWave) sym_pass<R, SPLIT, false, FORCES>(y, res, tw, cols, lane, valid, fx, fy, z64, z32);
+    else if (valid > 0) sym_pass<R, SPLIT, true, FORCES>(y, res, tw, cols, lane, valid, fx, fy, z64, z32);
+    if (FORCES) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) sh.rows[q][r][lane] = res[r];
+      if (vj) part[((int64_t)b * nb + a) * T + jl] = make_float2(fx, fy);
+    }
+    sh.z[q][lane] = SPLIT ? z64 : (double)z32;
+  }
+  __syncthreads();
+  if (!live) return;
+  if (FORCES) {
+    reg_pair sum = reg_pair{0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const reg_pair r = sh.rows[k][q][lane];
+      sum = reg_pair{sum.x + r.x, sum.y + r.y};
+    }
+    part[((int64_t)a * nb + b) * T + q * kWave + lane] = make_float2(sum.y, sum.x);
+  }
+  if (q != 0) return;
+  // every unordered pair stands for the two ordered pairs of Z
+  if (SPLIT) {
+    double z = sh.z[0][lane];
+#pragma unroll
+    for (int k = 1; k < R; ++k) z += sh.z[k][lane];
+    z = wave_sum(z);
+    if (lane == 0) zpart[item] = 2.0 * z;
+  } else {
+    float z = (float)sh.z[0][lane];
+#pragma unroll
+    for (int k = 1; k < R; ++k) z += (float)sh.z[k][lane];
+    z = wave_sum(z);
+    if (lane == 0) zpart32[item] = 2.0f * z;
+  }
+}
+
 // Direct tile: rows of block a against every valid column of block b.
 // SELF (a == b) masks the i == j term by index; MASK_I masks rows past n
 // (only the last block is partial).  Full off-diagonal tiles run unmasked.
@@ -438,10 +527,48 @@ constexpr int repulse_min_waves() {
   return R <= 4 ? 8 : R <= 8 ? 6 : R <= 16 ? 4 : 1;
 }
 
-// Workgroups that take one tile per wave; those after them take one of the
+// Workgroups of the off-diagonal tiles; those after them take one of the
 // n_diag diagonal tiles (the first of the list) each.
-__host__ __device__ __forceinline__ int64_t wave_tile_blocks(int64_t n_items, int64_t n_diag) {
-  return (n_items - n_diag + kWavesPerBlock - 1) / kWavesPerBlock;
+__host__ __device__ __forceinline__ int64_t wave_tile_blocks(int64_t n_items, int64_t n_diag, int R) {
+  const int per = tiles_per_block(R);
+  return (n_items - n_diag + per - 1) / per;
+}
+
+// LDS of a workgroup of off-diagonal tiles (or of a diagonal one, which uses
+// the columns only).
+template <int R>
+struct TileLds {
+  float2 cols[kWavesPerBlock][2 * kWave];
+  SharedTile<tile_waves<R>() == 1 ? 1 : R> tile[tile_waves<R>() == 1 ? 1 : kWavesPerBlock / tile_waves<R>()];
+};
+
+// The off-diagonal tiles of workgroup `block`: tile k of the list's n_off.
+// find(k, &view) gives a tile's graph and blocks, false if it is not to run.
+struct TileView {
+  const float2* Y;
+  float2* part;
+  double* zpart;
+  float* zpart32;
+  int64_t slot;  // of the Z partial
+  int32_t n, nb, a, b;
+};
+
+template <int R, bool SPLIT, bool FORCES, typename Find>
+__device__ __forceinline__ void off_diagonal_tiles(int64_t block, int64_t n_off, int wave, int lane, TileLds<R>& lds,
+                                                   Find find) {
+  constexpr int W = tile_waves<R>();
+  const int64_t k = block * tiles_per_block(R) + wave / W;
+  TileView v;
+  const bool live = k < n_off && find(k, &v);
+  if (W == 1) {
+    if (live)
+      tile_symmetric<R, SPLIT, FORCES>(v.Y, v.n, v.nb, v.a, v.b, v.part, v.zpart, v.zpart32, v.slot, lane,
+                                       lds.cols[wave]);
+  } else {
+    tile_symmetric_shared<W == 1 ? 1 : R, SPLIT, FORCES>(v.Y, v.n, v.nb, v.a, v.b, v.part, v.zpart, v.zpart32, v.slot,
+                                                         live, wave % W, lane, lds.cols[wave],
+                                                         lds.tile[W == 1 ? 0 : wave / W]);
+  }
 }
 
 template <int R, bool SPLIT, bool SYM>
@@ -452,20 +579,22 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_repulse(cons
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
   if (SYM) {
-    __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+    __shared__ TileLds<R> lds;
     __shared__ double s_z[kWavesPerBlock];
-    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
+    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag, R);
     if ((int64_t)blockIdx.x >= wave_blocks) {
       const int64_t item = (int64_t)blockIdx.x - wave_blocks;
       const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
-      tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+      tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
       return;
     }
-    const int64_t item = n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
-    if (item >= n_items) return;
-    const int2 ab = items[item];
-    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
-    tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, s_cols[wave]);
+    off_diagonal_tiles<R, SPLIT, true>(
+        blockIdx.x, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+          const int2 ab = items[n_diag + k];
+          *v = TileView{Y, part, zpart, zpart32, n_diag + k, n, nb, __builtin_amdgcn_readfirstlane(ab.x),
+                        __builtin_amdgcn_readfirstlane(ab.y)};
+          return true;
+        });
   } else {
     const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
     if (item >= n_items) return;
@@ -485,20 +614,22 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
   if (SYM) {
-    __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+    __shared__ TileLds<R> lds;
     __shared__ double s_z[kWavesPerBlock];
-    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag);
+    const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag, R);
     if ((int64_t)blockIdx.x >= wave_blocks) {
       const int64_t item = (int64_t)blockIdx.x - wave_blocks;
       const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
-      tile_diag<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+      tile_diag<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
       return;
     }
-    const int64_t item = n_diag + (int64_t)blockIdx.x * kWavesPerBlock + wave;
-    if (item >= n_items) return;
-    const int2 ab = items[item];
-    const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
-    tile_symmetric<R, SPLIT, false>(Y, n, nb, a, b, nullptr, zpart, zpart32, item, lane, s_cols[wave]);
+    off_diagonal_tiles<R, SPLIT, false>(
+        blockIdx.x, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+          const int2 ab = items[n_diag + k];
+          *v = TileView{Y, nullptr, zpart, zpart32, n_diag + k, n, nb, __builtin_amdgcn_readfirstlane(ab.x),
+                        __builtin_amdgcn_readfirstlane(ab.y)};
+          return true;
+        });
   } else {
     const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
     if (item >= n_items) return;
@@ -511,7 +642,7 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
 template <int R>
 hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag) + p.diag));
+  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag, R) + p.diag));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
@@ -532,7 +663,7 @@ hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int p
 template <int R>
 hipError_t launch_repulsion_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag) + p.diag));
+  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag, R) + p.diag));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
@@ -756,7 +887,7 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_forces(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const float* __restrict__ P,
     const int32_t* __restrict__ heavy, int32_t n_heavy, double2* __restrict__ attract, AttractBlocks mix,
     int32_t* __restrict__ tstep) {
-  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  __shared__ TileLds<R> lds;
   __shared__ double s_z[kWavesPerBlock];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
@@ -779,18 +910,19 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_forces(
     }
     return;
   }
-  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag);
+  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag, R);
   if (block >= wave_blocks) {
     const int64_t item = block - wave_blocks;
     const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
-    tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, s_cols[wave], s_z);
+    tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
     return;
   }
-  const int64_t item = n_diag + block * kWavesPerBlock + wave;
-  if (item >= n_items) return;
-  const int2 ab = items[item];
-  const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
-  tile_symmetric<R, SPLIT>(Y, n, nb, a, b, part, zpart, zpart32, item, lane, s_cols[wave]);
+  off_diagonal_tiles<R, SPLIT, true>(block, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+    const int2 ab = items[n_diag + k];
+    *v = TileView{Y, part, zpart, zpart32, n_diag + k, n, nb, __builtin_amdgcn_readfirstlane(ab.x),
+                  __builtin_amdgcn_readfirstlane(ab.y)};
+    return true;
+  });
 }
 
 // Plans of at most this many tiles have their Z summed by every workgroup of
@@ -986,7 +1118,7 @@ template <int R, bool SPLIT>
 __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_forces(
     const BatchDesc* __restrict__ descs, const int4* __restrict__ items, int64_t n_items, int64_t n_diag,
     const int2* __restrict__ chunks, const int2* __restrict__ heavy, int32_t n_heavy, AttractBlocks mix) {
-  __shared__ float2 s_cols[kWavesPerBlock][2 * kWave];
+  __shared__ TileLds<R> lds;
   __shared__ double s_z[kWavesPerBlock];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
@@ -1009,20 +1141,26 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_forces
     }
     return;
   }
-  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag);
-  const bool diag = block >= wave_blocks;
-  const int64_t item = diag ? block - wave_blocks : n_diag + block * kWavesPerBlock + wave;
-  if (item >= n_items) return;
-  const int4 it = items[item];
-  const int32_t gi = __builtin_amdgcn_readfirstlane(it.x);
-  const BatchDesc& d = descs[gi];
-  const int32_t a = __builtin_amdgcn_readfirstlane(it.y), b = __builtin_amdgcn_readfirstlane(it.z);
-  const int64_t li = __builtin_amdgcn_readfirstlane(it.w);
-  const bool live = batch_live(d);
-  if (diag && a == 0 && threadIdx.x == 0) *d.t_run = live ? *d.t + 1 : -1;
-  if (!live) return;
-  if (diag) tile_diag<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, li, wave, lane, s_cols[wave], s_z);
-  else tile_symmetric<R, SPLIT>(d.Y, d.n, d.nb, a, b, d.part, d.zpart, d.zpart32, li, lane, s_cols[wave]);
+  const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag, R);
+  if (block >= wave_blocks) {
+    const int4 it = items[block - wave_blocks];
+    const BatchDesc& d = descs[__builtin_amdgcn_readfirstlane(it.x)];
+    const int32_t a = __builtin_amdgcn_readfirstlane(it.y);
+    const bool live = batch_live(d);
+    if (a == 0 && threadIdx.x == 0) *d.t_run = live ? *d.t + 1 : -1;
+    if (live)
+      tile_diag<R, SPLIT>(d.Y, d.n, d.nb, a, d.part, d.zpart, d.zpart32, __builtin_amdgcn_readfirstlane(it.w), wave,
+                          lane, lds.cols[wave], s_z);
+    return;
+  }
+  off_diagonal_tiles<R, SPLIT, true>(block, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+    const int4 it = items[n_diag + k];
+    const BatchDesc& d = descs[__builtin_amdgcn_readfirstlane(it.x)];
+    if (!batch_live(d)) return false;
+    *v = TileView{d.Y, d.part, d.zpart, d.zpart32, __builtin_amdgcn_readfirstlane(it.w), d.n, d.nb,
+                  __builtin_amdgcn_readfirstlane(it.y), __builtin_amdgcn_readfirstlane(it.z)};
+    return true;
+  });
 }
 
 template <bool SPLIT>
@@ -1251,7 +1389,7 @@ template <int R>
 hipError_t launch_forces_r(const tsgne_graph* g, const float2* Y, bool split, int32_t* tstep, hipStream_t s) {
   const Workspace& ws = g->ws;
   const RepulsionPlan& p = ws.plan;
-  const int64_t tiles = wave_tile_blocks(p.items, p.diag) + p.diag;
+  const int64_t tiles = wave_tile_blocks(p.items, p.diag, R) + p.diag;
   const AttractBlocks mix = mix_attract(tiles, blocks_for((int64_t)g->n * kRowLanes, kBlock),
                                         blocks_for(g->n_heavy, kWavesPerBlock));
   const dim3 grid(mixed_grid(tiles, mix));
@@ -1328,7 +1466,7 @@ hipError_t launch_kl_ws(const tsgne_graph* g, const Workspace& ws, const float2*
 
 template <int R>
 hipError_t launch_batch_forces_r(const BatchPlan& bp, bool split, hipStream_t s) {
-  const int64_t tiles = wave_tile_blocks(bp.n_items, bp.n_diag) + bp.n_diag;
+  const int64_t tiles = wave_tile_blocks(bp.n_items, bp.n_diag, R) + bp.n_diag;
   const AttractBlocks mix = mix_attract(tiles, bp.n_light_chunks, blocks_for(bp.n_heavy, kWavesPerBlock));
   const dim3 grid(mixed_grid(tiles, mix));
   if (split)
