@@ -933,11 +933,12 @@ constexpr int64_t kOwnZItems = 8192;
 constexpr int kUpdateRows = kUpdateBlockRows;  // rows per workgroup of the update
 static_assert(kUpdateRows == kWave, "one row per lane");
 
-// Z of at most kOwnZItems tile partials by a workgroup of kBlock threads, to
-// every thread: the additions of zsum_block in its order, each thread standing
-// for four of its 1024, so bitwise the same Z.
+// Z of at most kOwnZItems tile partials by a workgroup of kBlock threads: the
+// additions of zsum_block in its order, each thread standing for four of its
+// 1024, so bitwise the same Z.  First each thread's part, then (block_Z) the
+// sum, to every thread.
 template <typename V>
-__device__ __forceinline__ V block_Z(const V* __restrict__ zpart, int32_t n_items, V* s_z) {
+__device__ __forceinline__ V thread_Z(const V* __restrict__ zpart, int32_t n_items) {
   constexpr int kPer = kZThreads / kBlock, kLoads = (int)(kOwnZItems / kZThreads);
   static_assert(kPer == 4 && kLoads == 8, "the combinations below add four threads' sums of eight loads");
   const int t = threadIdx.x;
@@ -953,7 +954,12 @@ __device__ __forceinline__ V block_Z(const V* __restrict__ zpart, int32_t n_item
     }
     a[p] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
   }
-  V z = (a[0] + a[2]) + (a[1] + a[3]);  // the tree's levels 512 and 256
+  return (a[0] + a[2]) + (a[1] + a[3]);  // the tree's levels 512 and 256
+}
+
+template <typename V>
+__device__ __forceinline__ V block_Z(V z, V* s_z) {
+  const int t = threadIdx.x;
   s_z[t] = z;
   __syncthreads();
   if (t < kWave) {
@@ -1008,11 +1014,36 @@ __device__ __forceinline__ void update_rows(const UpdateView& v, int32_t T, int3
   // a load makes the compiler wait for it before the next one is issued), so
   // past the last block an index is clamped to it: an in-bounds re-read that
   // adds +0, which leaves a sum started at +0 unchanged.
+  //
+  // The first batch's loads go out before anything waits, and with them those
+  // of Z's partials and of the rows' own state: one after the other these were
+  // three trips to memory of a 2,000-node update's 5.5 us.
   constexpr int kBatchLoads = 16;
-  for (int32_t o0 = first; o0 < end; o0 += kBatchLoads) {
-    float2 p[kBatchLoads];
+  float2 p[kBatchLoads];
 #pragma unroll
-    for (int u = 0; u < kBatchLoads; ++u) p[u] = pp[(int64_t)min(o0 + u, end - 1) * T];
+  for (int u = 0; u < kBatchLoads; ++u) p[u] = pp[(int64_t)max(min(first + u, end - 1), 0) * T];
+  const int32_t own = min(i, v.n - 1);
+  double2 A = make_double2(0.0, 0.0);
+  float2 y = make_float2(0.f, 0.f), uu = y, gn = y;
+  if (wave == 0) {
+    A = v.attract[own];
+    if (do_update) {
+      y = v.Y[own];
+      uu = v.U[own];
+      gn = v.G[own];
+    }
+  }
+  double z64 = 0.0;
+  float z32 = 0.f;
+  if (OWN_Z) {
+    if (SPLIT) z64 = thread_Z<double>(v.zpart, v.n_items);
+    else z32 = thread_Z<float>(v.zpart32, v.n_items);
+  }
+  for (int32_t o0 = first; o0 < end; o0 += kBatchLoads) {
+    if (o0 != first) {
+#pragma unroll
+      for (int u = 0; u < kBatchLoads; ++u) p[u] = pp[(int64_t)min(o0 + u, end - 1) * T];
+    }
     const int32_t count = end - o0;
 #pragma unroll
     for (int u = 0; u < kBatchLoads; ++u) {
@@ -1029,8 +1060,7 @@ __device__ __forceinline__ void update_rows(const UpdateView& v, int32_t T, int3
   s_r[wave][lane] = SPLIT ? make_double2(rx, ry) : make_double2(sx, sy);
   double Z;
   if (OWN_Z) {
-    Z = SPLIT ? block_Z<double>(v.zpart, v.n_items, s_z)
-              : (double)block_Z<float>(v.zpart32, v.n_items, reinterpret_cast<float*>(s_z));
+    Z = SPLIT ? block_Z<double>(z64, s_z) : (double)block_Z<float>(z32, reinterpret_cast<float*>(s_z));
   } else {
     Z = *v.Z;
     __syncthreads();
@@ -1053,7 +1083,6 @@ __device__ __forceinline__ void update_rows(const UpdateView& v, int32_t T, int3
       sy += (float)r.y;
     }
   }
-  const double2 A = v.attract[i];
   float2 g;
   if (SPLIT) {
     const double invZ = Z > 0.0 ? 1.0 / Z : 0.0;
@@ -1066,17 +1095,16 @@ __device__ __forceinline__ void update_rows(const UpdateView& v, int32_t T, int3
   }
   if (grad_out) grad_out[i] = g;
   if (!do_update) return;
-  float2 y = v.Y[i], u = v.U[i], gn = v.G[i];
-  gn.x = (g.x * u.x < 0.f) ? gn.x + 0.2f : gn.x * 0.8f;
-  gn.y = (g.y * u.y < 0.f) ? gn.y + 0.2f : gn.y * 0.8f;
+  gn.x = (g.x * uu.x < 0.f) ? gn.x + 0.2f : gn.x * 0.8f;
+  gn.y = (g.y * uu.y < 0.f) ? gn.y + 0.2f : gn.y * 0.8f;
   gn.x = fmaxf(gn.x, min_gain);
   gn.y = fmaxf(gn.y, min_gain);
-  u.x = momentum * u.x - eta * gn.x * g.x;
-  u.y = momentum * u.y - eta * gn.y * g.y;
-  y.x += u.x;
-  y.y += u.y;
+  uu.x = momentum * uu.x - eta * gn.x * g.x;
+  uu.y = momentum * uu.y - eta * gn.y * g.y;
+  y.x += uu.x;
+  y.y += uu.y;
   v.Y[i] = y;
-  v.U[i] = u;
+  v.U[i] = uu;
   v.G[i] = gn;
 }
 
