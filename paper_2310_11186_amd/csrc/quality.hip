@@ -171,6 +171,11 @@ __global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict
   extern __shared__ double2 s_c[];
   unsigned long long* s_sum = reinterpret_cast<unsigned long long*>(s_c + k);
   int32_t* s_cnt = reinterpret_cast<int32_t*>(s_sum + 2 * k);
+  const int sub = threadIdx.x & (kPointLanes - 1);
+  const int64_t i = (int64_t)blockIdx.x * kPassPoints + threadIdx.x / kPointLanes;
+  // this point's loads go out first, ahead of the waits for the state
+  const int2 pt = i < n ? q[i] : make_int2(0, 0);
+  const int32_t old = i < n ? labels[i] : 0;
   const bool keeper = blockIdx.x == 0;  // the workgroup that writes the state
   if (keeper && threadIdx.x == 0) st.moved[(p + 1) % 3] = 0;
   if (p > 1 && st.moved[(p - 1) % 3] == 0) {  // converged (uniform)
@@ -205,12 +210,9 @@ __global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict
     }
   }
   __syncthreads();
-  const int sub = threadIdx.x & (kPointLanes - 1);
-  const int64_t i = (int64_t)blockIdx.x * kPassPoints + threadIdx.x / kPointLanes;
   bool moved = false;
   if (i < n) {
 #pragma clang fp contract(off)
-    const int2 pt = q[i];
     const double px = (double)pt.x, py = (double)pt.y;
     int32_t best = 0;
     double bd = INFINITY;
@@ -232,7 +234,6 @@ __global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict
       }
     }
     if (sub == 0) {
-      const int32_t old = labels[i];
       moved = old != best;
       if (moved) {
         labels[i] = best;
