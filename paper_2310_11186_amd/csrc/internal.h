@@ -45,6 +45,7 @@ struct RepulsionPlan {
 
 struct Workspace {
   RepulsionPlan plan;
+  void* block = nullptr;        // one device allocation that holds the arrays below
   int2* items = nullptr;        // (a, b) per work item
   float2* part = nullptr;       // [nb][nb][T] force partials: part[k][o] = sum over block o acting on block k
   double* zpart = nullptr;      // [items] Z partial of each item (ordered pairs)
@@ -54,7 +55,7 @@ struct Workspace {
   double* klpart = nullptr;     // [kl_blocks] KL partial sums
   double* klout = nullptr;      // [1]
   int32_t* tstep = nullptr;     // [2] device step counter of a run: next step, step being run
-  double* pinned = nullptr;     // host-pinned scratch for read-backs
+  double* pinned = nullptr;     // host-pinned scratch for read-backs (allocated by the first)
   int32_t kl_blocks = 0;
 };
 
@@ -161,6 +162,7 @@ struct tsgne_graph {
   int64_t nnz = 0;
   int32_t d = 0;
   float perplexity = 0.f;
+  void* block = nullptr;        // one device allocation that holds the arrays below
   int32_t* row_ptr = nullptr;   // [n+1]
   int32_t* col = nullptr;       // [nnz]
   int32_t* mirror = nullptr;    // [nnz]
@@ -192,6 +194,22 @@ hipError_t dalloc(T** p, size_t count) {
   *p = nullptr;
   if (count == 0) count = 1;
   return hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+}
+
+// Lays arrays out one after the other, 256 bytes apart at least: offsets are
+// taken first, then one allocation, then the arrays.
+struct BlockLayout {
+  size_t bytes = 0;
+  template <typename T>
+  size_t add(size_t count) {
+    const size_t at = bytes;
+    bytes += (sizeof(T) * count + 255) & ~(size_t)255;
+    return at;
+  }
+};
+template <typename T>
+void at_offset(T** p, void* block, size_t offset) {
+  *p = reinterpret_cast<T*>(static_cast<char*>(block) + offset);
 }
 
 template <typename T>
