@@ -189,10 +189,12 @@ tsgne_status graph_structure(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   // other streams' work, unlike hipFree)
   ScratchBlock tmp;
   tmp.s = s;
-  const size_t o_counters = 256, o_partial = 512;
+  // check words and counters (read back together), then the row check's scratch
+  constexpr size_t kRead = kCheckWords + 2;
+  const size_t o_partial = (sizeof(uint32_t) * kRead + 255) & ~(size_t)255;
   TSGNE_HIP(scratch_alloc(&tmp.p, o_partial + sizeof(int2) * (size_t)row_check_blocks(n), s), "allocate CSR checks");
-  uint32_t* err = static_cast<uint32_t*>(tmp.p);
-  int32_t* counters = reinterpret_cast<int32_t*>(static_cast<char*>(tmp.p) + o_counters);
+  uint32_t* check = static_cast<uint32_t*>(tmp.p);
+  int32_t* counters = static_cast<int32_t*>(tmp.p) + kCheckWords;
   int2* partial = reinterpret_cast<int2*>(static_cast<char*>(tmp.p) + o_partial);
 
   const int32_t heavy_cap = (int32_t)std::min<int64_t>(n, nnz / (kHeavyDegree + 1) + 1);
@@ -221,33 +223,29 @@ tsgne_status graph_structure(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
             "copy row_ptr");
   if (nnz > 0)
     TSGNE_HIP(hipMemcpyAsync(g->col, col_d, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToDevice, s), "copy col");
-  TSGNE_HIP(hipMemsetAsync(err, 0, sizeof(uint32_t), s), "clear error word");
-  TSGNE_HIP(hipMemsetAsync(counters, 0, 2 * sizeof(int32_t), s), "clear counters");
+  TSGNE_HIP(hipMemsetAsync(check, 0, sizeof(uint32_t) * kRead, s), "clear check words");
 
-  // 1. row_ptr must be valid before any kernel indexes col with it.
-  TSGNE_HIP(launch_check_rows(g->row_ptr, n, nnz, kHeavyDegree, err, counters, partial, g->heavy, nullptr, heavy_cap, s),
+  // Row check and heavy rows; then columns, symmetry and mirror index, which
+  // skip themselves when row_ptr is not fit to index col with.
+  TSGNE_HIP(launch_check_rows(g->row_ptr, n, nnz, kHeavyDegree, check, counters, partial, g->heavy, nullptr, heavy_cap,
+                              s),
             "launch row check");
-  uint32_t host_err = 0;
-  int32_t host_counters[2] = {0, 0};
-  TSGNE_HIP(hipMemcpyAsync(&host_err, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "read error word");
-  TSGNE_HIP(hipMemcpyAsync(host_counters, counters, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s), "read counters");
-  TSGNE_HIP(hipStreamSynchronize(s), "synchronise row check");
-  if (host_err) return fail(TSGNE_E_GRAPH, "row_ptr is not nondecreasing from 0 to nnz");
-  g->nonisolated = host_counters[0];
-  g->n_heavy = std::min(host_counters[1], heavy_cap);
-
-  // 2. Column checks, symmetry, mirror index.
-  TSGNE_HIP(launch_mirror(g->row_ptr, g->col, n, nnz, g->mirror, g->row_of, err, s), "launch mirror");
-  TSGNE_HIP(hipMemcpyAsync(&host_err, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "read error word");
+  TSGNE_HIP(launch_mirror(g->row_ptr, g->col, n, nnz, g->mirror, g->row_of, check, s), "launch mirror");
+  uint32_t words[kRead];
+  TSGNE_HIP(hipMemcpyAsync(words, check, sizeof(words), hipMemcpyDeviceToHost, s), "read check words");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise CSR check");
-  if (host_err) {
+  const uint32_t errors = check_errors(words);
+  if (errors & kErrRowPtr) return fail(TSGNE_E_GRAPH, "row_ptr is not nondecreasing from 0 to nnz");
+  if (errors) {
     std::string why = "CSR is not canonical/symmetric:";
-    if (host_err & kErrColRange) why += " column outside [0, n);";
-    if (host_err & kErrSelfLoop) why += " self-loop;";
-    if (host_err & kErrOrder) why += " columns not strictly ascending;";
-    if (host_err & kErrAsym) why += " entry (i,j) without (j,i);";
+    if (errors & kErrColRange) why += " column outside [0, n);";
+    if (errors & kErrSelfLoop) why += " self-loop;";
+    if (errors & kErrOrder) why += " columns not strictly ascending;";
+    if (errors & kErrAsym) why += " entry (i,j) without (j,i);";
     return fail(TSGNE_E_GRAPH, why);
   }
+  g->nonisolated = (int32_t)words[kCheckWords];
+  g->n_heavy = std::min((int32_t)words[kCheckWords + 1], heavy_cap);
   guard.g = nullptr;
   *out = g;
   return TSGNE_OK;

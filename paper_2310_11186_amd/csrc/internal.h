@@ -32,6 +32,18 @@ enum : uint32_t {
   kErrAsym = 1u << 4,     // (i, j) stored without (j, i)
 };
 
+// Words the CSR check fills, cleared by the caller: the error word, then one
+// counter per kCheckStride words (a cache line each) that must sum to zero.
+constexpr int kCheckStride = 32;
+constexpr int kCheckCounters = 32;
+constexpr int kCheckWords = kCheckStride * (1 + kCheckCounters);
+// The error bits, from the words read back to the host.
+inline uint32_t check_errors(const uint32_t* words) {
+  uint32_t sum = 0;
+  for (int c = 1; c <= kCheckCounters; ++c) sum += words[c * kCheckStride];
+  return words[0] | (sum ? (uint32_t)kErrAsym : 0u);
+}
+
 // All-pairs repulsion plan: positions are cut into nb blocks of T = 64 * R;
 // tile (a, b) covers rows of block a against columns of block b.
 struct RepulsionPlan {
@@ -264,18 +276,19 @@ float effective_eta(const tsgne_graph* g, const tsgne_params* p);
 tsgne_status ensure_workspace(tsgne_graph* g, const tsgne_params* p);
 
 // Launchers (return hipSuccess or the first HIP error).
-// Checks row_ptr (err |= row bit) and selects, in ascending order, the rows
-// of degree above `threshold` into ids (int32) and/or recs (row, first,
-// end, 0), at most cap of them.  counters[0] = rows with entries,
-// counters[1] = selected rows.  partial: int2[row_check_blocks(n)] scratch.
+// Checks row_ptr (check[0] |= row bit) and, unless counters is NULL, selects, in
+// ascending order, the rows of degree above `threshold` into ids (int32)
+// and/or recs (row, first, end, 0), at most cap of them.  counters[0] = rows
+// with entries, counters[1] = selected rows.  partial: scratch of
+// int2[row_check_blocks(n)] for that.
 int64_t row_check_blocks(int32_t n);
-hipError_t launch_check_rows(const int32_t* row_ptr, int32_t n, int64_t nnz, int32_t threshold, uint32_t* err,
+hipError_t launch_check_rows(const int32_t* row_ptr, int32_t n, int64_t nnz, int32_t threshold, uint32_t* check,
                              int32_t* counters, int2* partial, int32_t* ids, int4* recs, int32_t cap,
                              hipStream_t s);
-// Fills row_of (the row of every entry) and checks columns and symmetry
-// (err |= column bits); mirror[e] = position of the reverse entry.
+// Fills row_of (the row of every entry) and checks columns and symmetry into
+// check; mirror[e] (nullable) = position of the reverse entry.
 hipError_t launch_mirror(const int32_t* row_ptr, const int32_t* col, int32_t n, int64_t nnz, int32_t* mirror,
-                         int32_t* row_of, uint32_t* err, hipStream_t s);
+                         int32_t* row_of, uint32_t* check, hipStream_t s);
 hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, int64_t nnz, const float* X, int32_t d,
                          double* D, hipStream_t s);
 hipError_t launch_calibrate(const int32_t* row_ptr, int32_t n, const int32_t* heavy, int32_t n_heavy, const double* D,

@@ -245,32 +245,25 @@ unsigned blocks_for(int64_t work) { return (unsigned)((work + kBlock - 1) / kBlo
 
 }  // namespace
 
-size_t validate_csr_bytes(int32_t n, int64_t nnz) {
-  return sizeof(int32_t) * (4 + 2 * (size_t)row_check_blocks(n) + 2 * (size_t)nnz);
-}
+size_t validate_csr_bytes(int32_t, int64_t nnz) { return sizeof(int32_t) * (kCheckWords + (size_t)nnz); }
 
 // Checks that (row_ptr, col) is a canonical symmetric CSR, in scratch of
-// validate_csr_bytes(n, nnz): error word, counters, per-block row counts,
-// mirror, row index.
+// validate_csr_bytes(n, nnz): check words, row index.
 tsgne_status validate_csr_in(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, void* scratch,
                              hipStream_t s, int32_t** row_of_out) {
-  const int64_t blocks = row_check_blocks(n);
-  int32_t* const buf = static_cast<int32_t*>(scratch);
-  uint32_t* const err = reinterpret_cast<uint32_t*>(buf);
-  int32_t* const counters = buf + 1;
-  int2* const partial = reinterpret_cast<int2*>(buf + 4);
-  int32_t* const mirror = buf + 4 + 2 * blocks;
-  int32_t* const row_of = mirror + nnz;
-  TSGNE_HIP(hipMemsetAsync(buf, 0, 4 * sizeof(int32_t), s), "clear error word and counters");
-  TSGNE_HIP(launch_check_rows(row_ptr, n, nnz, INT32_MAX, err, counters, partial, nullptr, nullptr, 0, s),
+  uint32_t* const check = static_cast<uint32_t*>(scratch);
+  int32_t* const row_of = static_cast<int32_t*>(scratch) + kCheckWords;
+  TSGNE_HIP(hipMemsetAsync(check, 0, sizeof(uint32_t) * kCheckWords, s), "clear check words");
+  TSGNE_HIP(launch_check_rows(row_ptr, n, nnz, INT32_MAX, check, nullptr, nullptr, nullptr, nullptr, 0, s),
             "launch row check");
   // the column checks skip themselves when the row check failed
-  TSGNE_HIP(launch_mirror(row_ptr, col, n, nnz, mirror, row_of, err, s), "launch CSR check");
-  uint32_t host_err = 0;
-  TSGNE_HIP(hipMemcpyAsync(&host_err, err, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "read error word");
+  TSGNE_HIP(launch_mirror(row_ptr, col, n, nnz, nullptr, row_of, check, s), "launch CSR check");
+  uint32_t words[kCheckWords];
+  TSGNE_HIP(hipMemcpyAsync(words, check, sizeof(words), hipMemcpyDeviceToHost, s), "read check words");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise CSR check");
-  if (host_err & kErrRowPtr) return fail(TSGNE_E_GRAPH, "row_ptr is not nondecreasing from 0 to nnz");
-  if (host_err) return fail(TSGNE_E_GRAPH, "CSR is not canonical and symmetric");
+  const uint32_t errors = check_errors(words);
+  if (errors & kErrRowPtr) return fail(TSGNE_E_GRAPH, "row_ptr is not nondecreasing from 0 to nnz");
+  if (errors) return fail(TSGNE_E_GRAPH, "CSR is not canonical and symmetric");
   if (row_of_out) *row_of_out = row_of;
   return TSGNE_OK;
 }
