@@ -68,6 +68,19 @@ def test_sp_star_and_isolated(gpu):
     assert np.all(X[1000:, 0] == 11.0) and X[1020, 2] == 0.0
 
 
+@pytest.mark.parametrize("n", [63, 64, 129, 7001])       # rows of a decoding block, one past two, hubs of 2 and 4 chunks
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 31, 32, 127, 255, 256])
+def test_sp_hubs_and_target_counts(gpu, n, d):
+    # two hubs, of all nodes and of every second one, whose levels alternate with a path of 14 off the last leaf
+    far = np.arange(2, n, 2)
+    edges = np.concatenate([star_edges(n), np.stack([np.ones_like(far), far], 1),
+                            n - 1 + path_edges(15)]).astype(np.int32)
+    targets = np.random.default_rng(n + d).choice(n + 14, d).astype(np.int32)
+    targets[-1] = n + 13                                                # 15 levels from the hub: past the first 12
+    X, oX, _ = run_both(gpu, n + 14, edges, targets, 1e6)
+    assert np.array_equal(X, oX)
+
+
 def test_sp_no_edges(gpu):
     import torch
     n = 40
