@@ -587,7 +587,7 @@ tsgne_status tsgne_build_P(int32_t n, int64_t nnz, const int32_t* row_ptr_d, con
   double* pcond = reinterpret_cast<double*>(static_cast<char*>(tmp.p) + o_pcond);
 
   // Distances, calibration, symmetrisation.
-  TSGNE_HIP(launch_sqdist(g->row_of, g->col, nnz, X_d, d, D, s), "launch distances");
+  TSGNE_HIP(launch_sqdist(g->row_of, g->col, g->mirror, nnz, X_d, d, D, s), "launch distances");
   TSGNE_HIP(launch_calibrate(g->row_ptr, n, g->heavy, g->n_heavy, D, (double)perplexity, pcond, g->beta, s),
             "launch calibration");
   const double S = 2.0 * (double)g->nonisolated;

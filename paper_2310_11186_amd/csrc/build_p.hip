@@ -235,26 +235,62 @@ __global__ __launch_bounds__(kBlock) void k_mirror(const int32_t* __restrict__ r
 // D_e = ||x_i - x_j||^2 (the squared distance of eq. (2)) from FP32 rows,
 // accumulated in FP64.  Sixteen lanes per entry stride over the d
 // coordinates (consecutive lanes read consecutive floats of a row).
+//
+// Bound by the rows gathered (d = 128, 800,000 entries: 820 MB, mostly from
+// beyond the L2).  An edge's two entries have the same distance to the last
+// bit, so the first of them computes it for both, and a group of lanes takes
+// two entries, their loads in groups: 92 -> 46 us.
 constexpr int kDistLanes = 16;
+constexpr int kDistPer = 2;  // entries per group of lanes
 
 __global__ __launch_bounds__(kBlock) void k_sqdist(const int32_t* __restrict__ row_of, const int32_t* __restrict__ col,
-                                                   int64_t nnz, const float* __restrict__ X, int32_t d,
-                                                   double* __restrict__ D) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t e = t / kDistLanes;
+                                                   const int32_t* __restrict__ mirror, int64_t nnz,
+                                                   const float* __restrict__ X, int32_t d, double* __restrict__ D) {
+  constexpr int64_t kGroups = kBlock / kDistLanes;
+  const int64_t e0 = (int64_t)blockIdx.x * kGroups * kDistPer + threadIdx.x / kDistLanes;
   const int sub = threadIdx.x & (kDistLanes - 1);
-  const bool live = e < nnz;
-  double acc = 0.0;
-  if (live) {
-    const float* xi = X + (int64_t)row_of[e] * d;
-    const float* xj = X + (int64_t)col[e] * d;
-    for (int32_t k = sub; k < d; k += kDistLanes) {
-      const double diff = (double)xi[k] - (double)xj[k];
-      acc = fma(diff, diff, acc);
+  int32_t other[kDistPer], row[kDistPer], far[kDistPer];
+#pragma unroll
+  for (int q = 0; q < kDistPer; ++q) {
+    const int64_t e = min(e0 + q * kGroups, nnz - 1);
+    other[q] = mirror[e];
+    row[q] = row_of[e];
+    far[q] = col[e];
+  }
+#pragma unroll
+  for (int q = 0; q < kDistPer; ++q) {
+    const int64_t e = e0 + q * kGroups;
+    const bool mine = e < nnz && e < other[q];  // the same for all lanes of the group
+    double acc = 0.0;
+    if (mine) {
+      const float* xi = X + (int64_t)row[q] * d;
+      const float* xj = X + (int64_t)far[q] * d;
+      constexpr int U = 4;  // coordinates per lane whose loads are issued together
+      int32_t k = sub;
+      for (; k + (U - 1) * kDistLanes < d; k += U * kDistLanes) {
+        float a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          a[u] = xi[k + u * kDistLanes];
+          b[u] = xj[k + u * kDistLanes];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const double diff = (double)a[u] - (double)b[u];
+          acc = fma(diff, diff, acc);
+        }
+      }
+      for (; k < d; k += kDistLanes) {
+        const double diff = (double)xi[k] - (double)xj[k];
+        acc = fma(diff, diff, acc);
+      }
+    }
+    for (int off = kDistLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kDistLanes);
+    if (mine && sub == 0) {
+      D[e] = acc;
+      D[other[q]] = acc;
     }
   }
-  for (int off = kDistLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kDistLanes);
-  if (live && sub == 0) D[e] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -355,25 +391,26 @@ __device__ void calibrate_row(const double* __restrict__ Dr, int64_t deg, double
   if (lane == 0) *beta_out = bt;
 }
 
-__global__ __launch_bounds__(kBlock) void k_calibrate_light(const int32_t* __restrict__ row_ptr, int32_t n,
-                                                            const double* __restrict__ D, double perp,
-                                                            double* __restrict__ pcond, double* __restrict__ beta) {
-  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kCalLanes;
+// The first heavy_blocks workgroups take the heavy rows, a wave each, the
+// others the light ones: hubs' rows, the longest chains, start first, and run
+// beside the rest (as two launches 56 + 47 us at 100,000 nodes, as one 60).
+__global__ __launch_bounds__(kBlock) void k_calibrate(const int32_t* __restrict__ row_ptr, int32_t n,
+                                                      const int32_t* __restrict__ heavy, int32_t n_heavy,
+                                                      int32_t heavy_blocks, const double* __restrict__ D, double perp,
+                                                      double* __restrict__ pcond, double* __restrict__ beta) {
+  if ((int32_t)blockIdx.x < heavy_blocks) {
+    const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6)));
+    if (w >= n_heavy) return;
+    const int32_t i = heavy[w];
+    const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
+    calibrate_row<kWave>(D + b, deg, perp, pcond + b, beta + i, (int)(threadIdx.x & (kWave - 1)));
+    return;
+  }
+  const int64_t i = ((int64_t)(blockIdx.x - heavy_blocks) * kBlock + threadIdx.x) / kCalLanes;
   if (i >= n) return;  // whole groups
   const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
   if (deg > kHeavyDegree) return;
   calibrate_row<kCalLanes>(D + b, deg, perp, pcond + b, beta + i, (int)(threadIdx.x & (kCalLanes - 1)));
-}
-
-__global__ __launch_bounds__(kBlock) void k_calibrate_heavy(const int32_t* __restrict__ row_ptr,
-                                                            const int32_t* __restrict__ heavy, int32_t n_heavy,
-                                                            const double* __restrict__ D, double perp,
-                                                            double* __restrict__ pcond, double* __restrict__ beta) {
-  const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6)));
-  if (w >= n_heavy) return;
-  const int32_t i = heavy[w];
-  const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
-  calibrate_row<kWave>(D + b, deg, perp, pcond + b, beta + i, (int)(threadIdx.x & (kWave - 1)));
 }
 
 // p_ij = (p_{j|i} + p_{i|j}) / S, eq. (3), with S = 2 * (non-isolated nodes).
@@ -413,22 +450,19 @@ hipError_t launch_mirror(const int32_t* row_ptr, const int32_t* col, int32_t n, 
   return hipGetLastError();
 }
 
-hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, int64_t nnz, const float* X, int32_t d, double* D,
-                         hipStream_t s) {
+hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, const int32_t* mirror, int64_t nnz,
+                         const float* X, int32_t d, double* D, hipStream_t s) {
   if (nnz == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sqdist, dim3(blocks_for(nnz * kDistLanes)), dim3(kBlock), 0, s, row_of, col, nnz, X, d, D);
+  hipLaunchKernelGGL(k_sqdist, dim3(blocks_for((nnz + kDistPer - 1) / kDistPer * kDistLanes)), dim3(kBlock), 0, s,
+                     row_of, col, mirror, nnz, X, d, D);
   return hipGetLastError();
 }
 
 hipError_t launch_calibrate(const int32_t* row_ptr, int32_t n, const int32_t* heavy, int32_t n_heavy, const double* D,
                             double perplexity, double* pcond, double* beta, hipStream_t s) {
-  hipLaunchKernelGGL(k_calibrate_light, dim3(blocks_for((int64_t)n * kCalLanes)), dim3(kBlock), 0, s, row_ptr, n, D, perplexity, pcond,
-                     beta);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || n_heavy == 0) return e;
-  const unsigned waves_per_block = kBlock / kWave;
-  hipLaunchKernelGGL(k_calibrate_heavy, dim3((n_heavy + waves_per_block - 1) / waves_per_block), dim3(kBlock), 0, s,
-                     row_ptr, heavy, n_heavy, D, perplexity, pcond, beta);
+  const int32_t heavy_blocks = (n_heavy + kBlock / kWave - 1) / (kBlock / kWave);
+  hipLaunchKernelGGL(k_calibrate, dim3(heavy_blocks + blocks_for((int64_t)n * kCalLanes)), dim3(kBlock), 0, s, row_ptr,
+                     n, heavy, n_heavy, heavy_blocks, D, perplexity, pcond, beta);
   return hipGetLastError();
 }
 

@@ -289,8 +289,8 @@ hipError_t launch_check_rows(const int32_t* row_ptr, int32_t n, int64_t nnz, int
 // check; mirror[e] (nullable) = position of the reverse entry.
 hipError_t launch_mirror(const int32_t* row_ptr, const int32_t* col, int32_t n, int64_t nnz, int32_t* mirror,
                          int32_t* row_of, uint32_t* check, hipStream_t s);
-hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, int64_t nnz, const float* X, int32_t d,
-                         double* D, hipStream_t s);
+hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, const int32_t* mirror, int64_t nnz,
+                         const float* X, int32_t d, double* D, hipStream_t s);
 hipError_t launch_calibrate(const int32_t* row_ptr, int32_t n, const int32_t* heavy, int32_t n_heavy, const double* D,
                             double perplexity, double* pcond, double* beta, hipStream_t s);
 hipError_t launch_symmetrise(const int32_t* mirror, int64_t nnz, const double* pcond, double S, float* P,

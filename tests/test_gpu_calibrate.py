@@ -53,3 +53,18 @@ def test_calibration_at_group_edges(gpu, kind, perp):
         H = np.log(e.sum()) + ex["beta"][i] * (d * e).sum() / e.sum()
         assert abs(H - np.log(np.float32(perp).astype(np.float64))) <= 1e-11, (i, DEGREES[i])
     g.close()
+
+
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 48, 63, 64, 65, 80, 127, 129])
+@pytest.mark.parametrize("cut", [0, 1])                  # an even and an odd number of edges
+def test_distances_at_group_edges(gpu, d, cut):
+    """Coordinates around the sixteen lanes of an entry and the four loads of a lane."""
+    import torch
+    n, edges, _ = star_graph("spread", 7)
+    edges = edges[:len(edges) - cut]
+    X = np.random.default_rng(d).standard_normal((n, d)).astype(np.float32)
+    rp, col = tsgne.tsgne_csr_from_edges(n, edges)
+    g = tsgne.tsgne_build_P(*(torch.from_numpy(a).to(gpu) for a in (rp, col, X)), 15.0)
+    P, _ = oracle.build_P(*oracle.csr_from_edges(n, edges), X, 15.0)
+    assert rel_l2(g.export()["P"], P) <= P_TOL
+    g.close()
