@@ -440,8 +440,7 @@ TSGNE_API tsgne_status tsgne_kl_noalloc(tsgne_graph* g, const float* Y_d, double
  * t = 0 .. n_iter[k]-1 with the schedule of p (early exaggeration and
  * momentum switch at p->exaggeration_iters).  Each step is one set of fused
  * launches for the whole batch (repulsion tiles of every graph, per-graph Z,
- * attraction, update), captured once as a HIP graph and replayed.  All graphs
- * use the repulsion tile p->tile_rows (1, 2, 4, 8, 12, 14, 15, 16; 0 = chosen from the batch's
+ * attraction, update).  All graphs use the repulsion tile p->tile_rows (1, 2, 4, 8, 12, 14, 15, 16; 0 = chosen from the batch's
  * total tile count) with symmetric tiles; each graph's arithmetic and
  * reduction order are its own, so its result equals tsgne_run of that graph
  * alone with the same tile_rows and the symmetric repulsion, bit for bit.
@@ -472,8 +471,7 @@ TSGNE_API tsgne_status tsgne_autotune(tsgne_graph* const* graphs, const float* c
  * tsgne_batch_run with a repulsion tile per graph: tile_rows[k] (1, 2, 4, 8,
  * 12, 14, 15, 16; 0 = the single-graph plan's choice for graph k's size).
  * The graphs of each tile size form one batched plan; the plans run side by
- * side (one branch stream each, forked and joined inside each captured chunk
- * of steps).  Graph k's layout equals tsgne_run of it alone with tile_rows[k]
+ * side (one branch stream each, forked and joined around the steps).  Graph k's layout equals tsgne_run of it alone with tile_rows[k]
  * and the symmetric repulsion, bit for bit.  Arguments, errors and
  * synchronisation as tsgne_batch_run.
  */
@@ -509,7 +507,7 @@ TSGNE_API tsgne_status tsgne_autotune_tiles(tsgne_graph* const* graphs, const fl
  * current device.  Requests are copied in at submission and queued; a worker
  * thread admits them while their estimated device footprint fits the budget
  * (building P on admission), advances the active requests in rounds of one
- * batched, graph-captured launch sequence (each request at its own step
+ * batched launch sequence (each request at its own step
  * index), and completes requests that reach n_iter (layout copied out, device
  * memory released).  With round_ms > 0 each round aims at that much GPU time
  * and shares it out as steps (at least 1, at most steps_per_round) by
@@ -579,7 +577,7 @@ typedef struct tsgne_server_stats {
   double busy_s;                  /* time spent in rounds */
   double admit_s;                 /* worker time spent admitting requests (uploads and affinities; mostly
                                      while a round runs on the GPU) */
-  double plan_s;                  /* worker time spent between rounds on plans, captures and shares */
+  double plan_s;                  /* worker time spent between rounds on plans and shares */
   double latency_p50_ms, latency_p99_ms, latency_mean_ms; /* submission to completion, completed requests */
   double layouts_per_s;           /* completed / (last completion - first submission) */
 } tsgne_server_stats;

@@ -1,6 +1,6 @@
 // Batched optimisation of many independent graphs: one set of fused launches
-// per step for the whole batch, captured once as a HIP graph and replayed, and
-// the autotuner that picks the repulsion tile for a batch by timing it.
+// per step for the whole batch, and the autotuner that picks the repulsion
+// tile for a batch by timing it.
 #include <algorithm>
 #include <cctype>
 #include <climits>
@@ -120,36 +120,6 @@ tsgne_status BatchRun::setup(const BatchMember* m, int32_t count, int32_t R, con
   return TSGNE_OK;
 }
 
-tsgne_status run_batch_steps(const BatchRun& br, const tsgne_params* p, int32_t n_steps, int32_t chunk,
-                             hipStream_t s) {
-  if (n_steps <= 0) return TSGNE_OK;
-  chunk = std::max(1, std::min(chunk, n_steps));
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  TSGNE_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t le = hipSuccess;
-  for (int32_t k = 0; k < chunk && le == hipSuccess; ++k) le = launch_batch_step(br.plan(), *p, s);
-  hipError_t ce = hipStreamEndCapture(s, &graph);
-  if (le != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return hip_fail(le, "launch batched step during capture");
-  }
-  TSGNE_HIP(ce, "end capture");
-  hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    return hip_fail(e, "instantiate batch graph");
-  }
-  const int32_t replays = (n_steps + chunk - 1) / chunk;
-  for (int32_t r = 0; r < replays && e == hipSuccess; ++r) e = hipGraphLaunch(exec, s);
-  hipError_t se = hipStreamSynchronize(s);
-  (void)hipGraphExecDestroy(exec);
-  (void)hipGraphDestroy(graph);
-  TSGNE_HIP(e, "launch batch graph");
-  TSGNE_HIP(se, "synchronise batch");
-  return TSGNE_OK;
-}
-
 // Streams and events to run several batched plans side by side.
 struct Branches {
   hipStream_t stream[kMaxTileKinds] = {};
@@ -170,24 +140,28 @@ struct Branches {
   }
 };
 
-// One batched step of every plan: with one plan on s itself, with several
-// each on its own branch stream, forked from s and joined back into it.
-hipError_t launch_groups_step(const std::vector<const BatchRun*>& runs, const tsgne_params& p, const Branches& br,
-                              hipStream_t s) {
-  if (runs.size() == 1) return launch_batch_step(runs[0]->plan(), p, s);
-  hipError_t e = hipEventRecord(br.fork, s);
-  for (size_t k = 0; k < runs.size() && e == hipSuccess; ++k) {
-    e = hipStreamWaitEvent(br.stream[k], br.fork, 0);
-    if (e == hipSuccess) e = launch_batch_step(runs[k]->plan(), p, br.stream[k]);
-    if (e == hipSuccess) e = hipEventRecord(br.join[k], br.stream[k]);
+// n_steps batched steps of every plan: with one plan on s itself, with several
+// each on its own branch stream, forked from s and joined back into it, step by
+// step in turn so that no branch waits for another's launches.
+//
+// Launched as they are: a batch's steps take the GPU longer than the host, and
+// to capture and instantiate 16 of them first left it idle for 0.2 ms.
+hipError_t launch_groups_steps(const std::vector<const BatchRun*>& runs, const tsgne_params& p, int32_t n_steps,
+                               const Branches& br, hipStream_t s) {
+  const bool fork = runs.size() > 1;
+  hipError_t e = fork ? hipEventRecord(br.fork, s) : hipSuccess;
+  for (size_t k = 0; fork && k < runs.size() && e == hipSuccess; ++k) e = hipStreamWaitEvent(br.stream[k], br.fork, 0);
+  for (int32_t t = 0; t < n_steps; ++t)
+    for (size_t k = 0; k < runs.size() && e == hipSuccess; ++k)
+      e = launch_batch_step(runs[k]->plan(), p, fork ? br.stream[k] : s);
+  for (size_t k = 0; fork && k < runs.size() && e == hipSuccess; ++k) {
+    e = hipEventRecord(br.join[k], br.stream[k]);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, br.join[k], 0);
   }
   return e;
 }
 
 namespace {
-
-constexpr int kCaptureSteps = 25;  // steps per captured HIP graph
 
 // Optimiser state (U = 0, gains = 1, t = 0, no pause limit) for a list of
 // graphs, contiguous.
@@ -251,18 +225,18 @@ int32_t default_batch_R(tsgne_graph* const* gs, int32_t count) {
   return 4;
 }
 
-// A stream that can be captured: the caller's, or a private one for NULL.
-struct CaptureStream {
+// The caller's stream, or a private one for NULL.
+struct RunStream {
   hipStream_t s = nullptr;
   bool owned = false;
-  explicit CaptureStream(void* user) {
+  explicit RunStream(void* user) {
     s = reinterpret_cast<hipStream_t>(user);
     if (!s) {
       if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess) owned = true;
       else s = nullptr;
     }
   }
-  ~CaptureStream() {
+  ~RunStream() {
     if (owned) (void)hipStreamDestroy(s);
   }
 };
@@ -287,48 +261,14 @@ struct TiledBatch {
   }
 };
 
-// Runs n_steps steps of several plans side by side: `chunk` steps captured
-// once (fork and join included) and replayed.  Synchronises s.
-tsgne_status run_groups(const std::vector<const BatchRun*>& runs, const tsgne_params* p, int32_t n_steps,
-                        int32_t chunk, const Branches& br, hipStream_t s) {
-  if (n_steps <= 0) return TSGNE_OK;
-  chunk = std::max(1, std::min(chunk, n_steps));
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  TSGNE_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t le = hipSuccess;
-  for (int32_t k = 0; k < chunk && le == hipSuccess; ++k) le = launch_groups_step(runs, *p, br, s);
-  hipError_t ce = hipStreamEndCapture(s, &graph);
-  if (le != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return hip_fail(le, "launch batched step during capture");
-  }
-  TSGNE_HIP(ce, "end capture");
-  hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    return hip_fail(e, "instantiate batch graph");
-  }
-  const int32_t replays = (n_steps + chunk - 1) / chunk;
-  for (int32_t r = 0; r < replays && e == hipSuccess; ++r) e = hipGraphLaunch(exec, s);
-  hipError_t se = hipStreamSynchronize(s);
-  (void)hipGraphExecDestroy(exec);
-  (void)hipGraphDestroy(graph);
-  TSGNE_HIP(e, "launch batch graph");
-  TSGNE_HIP(se, "synchronise batch");
-  return TSGNE_OK;
-}
-
-// Finiteness of the final layouts.
-tsgne_status check_layouts(tsgne_graph* const* graphs, float* const* Y_d, int32_t count, hipStream_t s) {
+// Finiteness of the final layouts, one launch per plan.
+tsgne_status check_layouts(const std::vector<const BatchRun*>& runs, hipStream_t s) {
   ScratchBlock flag;
   flag.s = s;
   TSGNE_HIP(scratch_alloc(&flag.p, sizeof(uint32_t), s), "allocate flag");
   uint32_t* f = static_cast<uint32_t*>(flag.p);
   TSGNE_HIP(hipMemsetAsync(f, 0, sizeof(uint32_t), s), "clear flag");
-  for (int32_t k = 0; k < count; ++k)
-    TSGNE_HIP(launch_nonfinite_check(reinterpret_cast<const float2*>(Y_d[k]), graphs[k]->n, f, s),
-              "launch finiteness check");
+  for (const BatchRun* r : runs) TSGNE_HIP(launch_batch_nonfinite_check(r->plan(), f, s), "launch finiteness check");
   uint32_t host_flag = 0;
   TSGNE_HIP(hipMemcpyAsync(&host_flag, f, sizeof(uint32_t), hipMemcpyDeviceToHost, s), "read flag");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise batch");
@@ -447,7 +387,7 @@ tsgne_status tsgne_batch_run(tsgne_graph* const* graphs, float* const* Y_d, cons
     max_iter = std::max(max_iter, n_iter[k]);
   }
   DeviceGuard dg(graphs[0]->device);
-  CaptureStream cs(stream);
+  RunStream cs(stream);
   if (!cs.s) return fail(TSGNE_E_DEVICE, "cannot create a stream");
   const int32_t R = p->tile_rows ? p->tile_rows : default_batch_R(graphs, count);
   PooledState ps;
@@ -455,22 +395,8 @@ tsgne_status tsgne_batch_run(tsgne_graph* const* graphs, float* const* Y_d, cons
   if (tsgne_status st = ps.make(graphs, Y_d, n_iter, count, members, cs.s)) return st;
   BatchRun br;
   if (tsgne_status st = br.setup(members.data(), count, R, p)) return st;
-  if (tsgne_status st = run_batch_steps(br, p, max_iter, kCaptureSteps, cs.s)) return st;
-  uint32_t* flag = nullptr;
-  TSGNE_HIP(dalloc(&flag, 1), "allocate flag");
-  struct F {
-    uint32_t*& f;
-    ~F() { dfree(f); }
-  } ff{flag};
-  TSGNE_HIP(hipMemsetAsync(flag, 0, sizeof(uint32_t), cs.s), "clear flag");
-  for (int32_t k = 0; k < count; ++k)
-    TSGNE_HIP(launch_nonfinite_check(reinterpret_cast<const float2*>(Y_d[k]), graphs[k]->n, flag, cs.s),
-              "launch finiteness check");
-  uint32_t host_flag = 0;
-  TSGNE_HIP(hipMemcpyAsync(&host_flag, flag, sizeof(uint32_t), hipMemcpyDeviceToHost, cs.s), "read flag");
-  TSGNE_HIP(hipStreamSynchronize(cs.s), "synchronise batch");
-  if (host_flag) return fail(TSGNE_E_NONFINITE, "a layout holds a NaN or infinity");
-  return TSGNE_OK;
+  for (int32_t t = 0; t < max_iter; ++t) TSGNE_HIP(launch_batch_step(br.plan(), *p, cs.s), "launch batched step");
+  return check_layouts({&br}, cs.s);
 }
 
 tsgne_status tsgne_autotune(tsgne_graph* const* graphs, const float* const* Y_d, int32_t count,
@@ -480,7 +406,7 @@ tsgne_status tsgne_autotune(tsgne_graph* const* graphs, const float* const* Y_d,
   if (steps < 1) return fail(TSGNE_E_INVAL, "steps must be >= 1");
   if (tsgne_status st = check_batch_args(graphs, Y_d, count, p)) return st;
   DeviceGuard dg(graphs[0]->device);
-  CaptureStream cs(stream);
+  RunStream cs(stream);
   if (!cs.s) return fail(TSGNE_E_DEVICE, "cannot create a stream");
   std::vector<float*> scratch((size_t)count, nullptr);
   struct Scratch {
@@ -548,14 +474,14 @@ tsgne_status tsgne_batch_run_tiles(tsgne_graph* const* graphs, float* const* Y_d
     max_iter = std::max(max_iter, n_iter[k]);
   }
   DeviceGuard dg(graphs[0]->device);
-  CaptureStream cs(stream);
+  RunStream cs(stream);
   if (!cs.s) return fail(TSGNE_E_DEVICE, "cannot create a stream");
   Branches br;
   if (!br.ok) return fail(TSGNE_E_DEVICE, "cannot create branch streams");
   TiledBatch tb;
   if (tsgne_status st = tb.setup(graphs, Y_d, n_iter, tiles.data(), count, p, cs.s)) return st;
-  if (tsgne_status st = run_groups(tb.order, p, max_iter, kCaptureSteps, br, cs.s)) return st;
-  return check_layouts(graphs, Y_d, count, cs.s);
+  TSGNE_HIP(launch_groups_steps(tb.order, *p, max_iter, br, cs.s), "launch batched steps");
+  return check_layouts(tb.order, cs.s);
 }
 
 tsgne_status tsgne_autotune_tiles(tsgne_graph* const* graphs, const float* const* Y_d, int32_t count,
@@ -565,7 +491,7 @@ tsgne_status tsgne_autotune_tiles(tsgne_graph* const* graphs, const float* const
   if (steps < 1) return fail(TSGNE_E_INVAL, "steps must be >= 1");
   if (tsgne_status st = check_batch_args(graphs, Y_d, count, p)) return st;
   DeviceGuard dg(graphs[0]->device);
-  CaptureStream cs(stream);
+  RunStream cs(stream);
   if (!cs.s) return fail(TSGNE_E_DEVICE, "cannot create a stream");
   Branches br;
   if (!br.ok) return fail(TSGNE_E_DEVICE, "cannot create branch streams");
@@ -614,9 +540,9 @@ tsgne_status tsgne_autotune_tiles(tsgne_graph* const* graphs, const float* const
                 "copy layout");
     TiledBatch tb;
     if (tsgne_status st = tb.setup(graphs, scratch.data(), iters.data(), tiles.data(), count, p, cs.s)) return st;
-    TSGNE_HIP(launch_groups_step(tb.order, *p, br, cs.s), "warm-up step");
+    TSGNE_HIP(launch_groups_steps(tb.order, *p, 1, br, cs.s), "warm-up step");
     TSGNE_HIP(hipEventRecord(e0, cs.s), "record event");
-    for (int32_t k = 0; k < steps; ++k) TSGNE_HIP(launch_groups_step(tb.order, *p, br, cs.s), "timed step");
+    TSGNE_HIP(launch_groups_steps(tb.order, *p, steps, br, cs.s), "timed steps");
     TSGNE_HIP(hipEventRecord(e1, cs.s), "record event");
     TSGNE_HIP(hipEventSynchronize(e1), "synchronise autotune");
     float t = 0.f;

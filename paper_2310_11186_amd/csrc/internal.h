@@ -145,11 +145,6 @@ class BatchRun {
   void* tables_ = nullptr;
 };
 
-// Runs n_steps batched steps: one captured sequence of up to `chunk` steps,
-// replayed (graphs past their n_iter skip their work).  Synchronises s.
-tsgne_status run_batch_steps(const BatchRun& br, const tsgne_params* p, int32_t n_steps, int32_t chunk,
-                             hipStream_t s);
-
 // Distinct repulsion tile sizes (1, 2, 4, 8, 12, 14, 15, 16).
 constexpr int kMaxTileKinds = 8;
 
@@ -322,6 +317,8 @@ hipError_t launch_kl_ws(const tsgne_graph* g, const Workspace& ws, const float2*
 // Start of a run: U = 0, gains = 1, the step counter and the flag 0.
 hipError_t launch_run_init(float2* U, float2* gains, int32_t n, int32_t* tstep, uint32_t* flag, hipStream_t s);
 hipError_t launch_nonfinite_check(const float2* Y, int32_t n, uint32_t* flag, hipStream_t s);
+// The same of every layout of a batch.
+hipError_t launch_batch_nonfinite_check(const BatchPlan& bp, uint32_t* flag, hipStream_t s);
 hipError_t launch_batch_step(const BatchPlan& bp, const tsgne_params& p, hipStream_t s);
 
 // Rows per lane for which the repulsion kernels are compiled.

@@ -4,10 +4,9 @@
 // device work.  It runs rounds: each active request is given a number of
 // steps (its share of the round's target time, by the share policy; by
 // default short requests first and long ones one at a time in submission
-// order), and every group of requests with the same tile size replays a
-// captured chunk of batched steps (each request at its own step index,
-// pausing on the device at its allotment) on its own branch stream, the
-// groups running together.  While a round runs, queued requests are admitted
+// order), and every group of requests with the same tile size takes batched
+// steps (each request at its own step index, pausing on the device at its
+// allotment) on its own branch stream, the groups running together.  While a round runs, queued requests are admitted
 // as their estimated device footprint fits the budget (their affinities built
 // on a stream of their own); they join the next round.  Requests that reached
 // n_iter complete at the round's end (layout copied out, memory released).
@@ -114,10 +113,6 @@ struct tsgne_server {
   int device = 0;
   std::thread worker, admitter;
   std::mutex mu;
-  // Held while the worker captures a chunk and while the admitter builds a
-  // request: a build's synchronous HIP calls (hipMalloc, hipMemcpy on the null
-  // stream) must not run while a stream is being captured.
-  std::mutex capture_mu;
   std::condition_variable cv_work, cv_done, cv_admit;
   std::deque<std::shared_ptr<Request>> queue;
   std::map<uint64_t, std::shared_ptr<Request>> all;
@@ -285,11 +280,8 @@ void tsgne_server::admit_loop() {
       building = 1;
     }
     const Clock::time_point t0 = Clock::now();
-    tsgne_status st;
-    {
-      std::lock_guard<std::mutex> cl(capture_mu);
-      st = stream_ok ? build_slot(*r, r->R, s, sl) : fail(TSGNE_E_DEVICE, "create the admission stream");
-    }
+    const tsgne_status st =
+        stream_ok ? build_slot(*r, r->R, s, sl) : fail(TSGNE_E_DEVICE, "create the admission stream");
     const std::string why = st == TSGNE_OK ? std::string() : std::string(tsgne_last_error());
     if (st != TSGNE_OK) finish(sl, st, why, false, s);
     std::lock_guard<std::mutex> lk(mu);
@@ -308,51 +300,19 @@ void tsgne_server::admit_loop() {
 
 namespace {
 
-// Steps of one captured chunk of a group (replayed as often as a round needs).
-constexpr int32_t kChunkSteps = 64;
-
-// The active requests of one tile size: their batched plan, the members'
-// tickets in plan order, and the captured chunks of that plan by length.
+// The active requests of one tile size: their batched plan and the members'
+// tickets in plan order.
 struct Group {
   BatchRun run;
   std::vector<uint64_t> tickets;
-  std::map<int32_t, hipGraphExec_t> chunks;
-  ~Group() { clear(); }
-  void clear() {
-    for (auto& kv : chunks) (void)hipGraphExecDestroy(kv.second);
-    chunks.clear();
-  }
 };
-
-// A captured chunk of `len` batched steps of a group's plan.
-tsgne_status chunk_exec(Group& gr, int32_t len, const tsgne_params& p, hipStream_t cap, hipGraphExec_t* out) {
-  auto it = gr.chunks.find(len);
-  if (it != gr.chunks.end()) {
-    *out = it->second;
-    return TSGNE_OK;
-  }
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  TSGNE_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t le = hipSuccess;
-  for (int32_t k = 0; k < len && le == hipSuccess; ++k) le = launch_batch_step(gr.run.plan(), p, cap);
-  hipError_t e = hipStreamEndCapture(cap, &graph);
-  if (e == hipSuccess) e = le;
-  if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (graph) (void)hipGraphDestroy(graph);
-  if (e != hipSuccess) return hip_fail(e, "capture a serving chunk");
-  gr.chunks[len] = exec;
-  *out = exec;
-  return TSGNE_OK;
-}
 
 }  // namespace
 
 void tsgne_server::run() {
   (void)hipSetDevice(device);
-  hipStream_t s = nullptr, cap = nullptr;
-  bool streams_ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess &&
-                    hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) == hipSuccess;
+  hipStream_t s = nullptr;
+  const bool streams_ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
   int32_t* limits = nullptr;  // per-slot pause step of the current round, indexed by slot id
   if (dalloc(&limits, (size_t)cfg.max_active) != hipSuccess) limits = nullptr;
   std::vector<int32_t> lim_host((size_t)cfg.max_active, 0);
@@ -533,7 +493,7 @@ void tsgne_server::run() {
       pairs += per_step_of(k) * take[k];
     }
     // Re-plan the groups whose membership changed (the others keep their
-    // plans and captured chunks).
+    // plans).
     if (st == TSGNE_OK) {
       std::map<int32_t, std::vector<size_t>> by_tile;
       for (size_t k = 0; k < active.size(); ++k)
@@ -550,7 +510,6 @@ void tsgne_server::run() {
         for (size_t k : kv.second) tickets.push_back(active[k].req->ticket);
         Group& gr = groups[kv.first];
         if (gr.tickets == tickets) continue;
-        gr.clear();
         gr.tickets.clear();
         std::vector<BatchMember> members;
         for (size_t k : kv.second) {
@@ -564,34 +523,27 @@ void tsgne_server::run() {
       }
     }
 
-    // Each group replays a captured chunk of its own length (the power of two
-    // at or above its longest allotment, at most kChunkSteps) as often as that
-    // allotment needs; members pause at their limit on the device, so a group
-    // of large graphs that take one step in a round does not launch the many
-    // steps a group of small ones takes beside it.
+    // Each group takes the steps of its longest allotment; members pause at
+    // their limit on the device, so a group of large graphs that take one step
+    // in a round does not launch the many steps a group of small ones takes
+    // beside it.
     // The groups run together, except the running long request's group,
     // which runs after them: the long request fills the GPU by itself, and
     // small graphs' steps beside its kernels cost it more than they gain;
     // the small requests, batched together, take about the time one of them
     // takes alone.
+    //
+    // Steps are launched as they are, the groups' in turn.  Captured in chunks
+    // (anew whenever a group's members changed, with admissions locked out) a
+    // burst of twelve requests of 1,000 to 30,000 nodes took 18.0 ms, now 16.1 to 17.0.
     struct Launch {
-      hipGraphExec_t exec;
-      int32_t reps;
-      bool after;
+      const BatchPlan* plan;
+      int32_t steps;
     };
-    std::vector<Launch> launches;
+    std::vector<Launch> together, after;
     for (auto& kv : groups) {
-      if (st != TSGNE_OK) break;
       const int32_t most = longest[kv.first];
-      if (most <= 0) continue;  // every member pauses: nothing to launch
-      int32_t len = 1;
-      while (len < most && len < kChunkSteps) len *= 2;
-      hipGraphExec_t exec = nullptr;
-      {
-        std::lock_guard<std::mutex> cl(capture_mu);
-        st = chunk_exec(kv.second, len, cfg.params, cap, &exec);
-      }
-      launches.push_back(Launch{exec, (most + len - 1) / len, kv.first >= kHeadKey});
+      if (most > 0) (kv.first >= kHeadKey ? after : together).push_back(Launch{&kv.second.run.plan(), most});
     }
     if (st == TSGNE_OK) {
       hipError_t e = hipMemcpyAsync(limits, lim_host.data(), sizeof(int32_t) * lim_host.size(),
@@ -605,22 +557,20 @@ void tsgne_server::run() {
     const Clock::time_point t0 = Clock::now();
     if (st == TSGNE_OK) {
       hipError_t e = hipSuccess;
-      std::vector<const Launch*> together, after;
-      for (const Launch& l : launches) (l.after ? after : together).push_back(&l);
-      if (together.size() == 1) {
-        for (int32_t r = 0; r < together[0]->reps && e == hipSuccess; ++r) e = hipGraphLaunch(together[0]->exec, s);
-      } else if (together.size() > 1) {
-        e = hipEventRecord(fork, s);
-        for (size_t gi = 0; gi < together.size() && e == hipSuccess; ++gi) {
-          e = hipStreamWaitEvent(branch[gi], fork, 0);
-          for (int32_t r = 0; r < together[gi]->reps && e == hipSuccess; ++r)
-            e = hipGraphLaunch(together[gi]->exec, branch[gi]);
-          if (e == hipSuccess) e = hipEventRecord(join[gi], branch[gi]);
-          if (e == hipSuccess) e = hipStreamWaitEvent(s, join[gi], 0);
-        }
+      const size_t forks = together.size() > 1 ? together.size() : 0;
+      if (forks) e = hipEventRecord(fork, s);
+      for (size_t gi = 0; gi < forks && e == hipSuccess; ++gi) e = hipStreamWaitEvent(branch[gi], fork, 0);
+      int32_t most = 0;
+      for (const Launch& l : together) most = std::max(most, l.steps);
+      for (int32_t t = 0; t < most; ++t)
+        for (size_t gi = 0; gi < together.size() && e == hipSuccess; ++gi)
+          if (t < together[gi].steps) e = launch_batch_step(*together[gi].plan, cfg.params, forks ? branch[gi] : s);
+      for (size_t gi = 0; gi < forks && e == hipSuccess; ++gi) {
+        e = hipEventRecord(join[gi], branch[gi]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, join[gi], 0);
       }
-      for (const Launch* l : after)
-        for (int32_t r = 0; r < l->reps && e == hipSuccess; ++r) e = hipGraphLaunch(l->exec, s);
+      for (const Launch& l : after)
+        for (int32_t t = 0; t < l.steps && e == hipSuccess; ++t) e = launch_batch_step(*l.plan, cfg.params, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e != hipSuccess) st = hip_fail(e, "run a serving round");
     }
@@ -686,8 +636,7 @@ void tsgne_server::run() {
     if (join[k]) (void)hipEventDestroy(join[k]);
   }
   if (fork) (void)hipEventDestroy(fork);
-  for (hipStream_t q : {s, cap})
-    if (q) (void)hipStreamDestroy(q);
+  if (s) (void)hipStreamDestroy(s);
 }
 
 extern "C" {

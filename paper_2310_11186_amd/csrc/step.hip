@@ -1281,6 +1281,16 @@ __global__ __launch_bounds__(kBlock) void k_nonfinite(const float2* __restrict__
   if (!isfinite(y.x) || !isfinite(y.y)) atomicOr(flag, 1u);
 }
 
+__global__ __launch_bounds__(kUpdateRows) void k_batch_nonfinite(const BatchDesc* __restrict__ descs,
+                                                                 const int2* __restrict__ blocks,
+                                                                 uint32_t* __restrict__ flag) {
+  const int2 bl = blocks[blockIdx.x];
+  const int32_t i = bl.y + (int32_t)threadIdx.x;
+  if (i >= descs[bl.x].n) return;
+  const float2 y = descs[bl.x].Y[i];
+  if (!isfinite(y.x) || !isfinite(y.y)) atomicOr(flag, 1u);
+}
+
 __global__ __launch_bounds__(kBlock) void k_run_init(float2* __restrict__ U, float2* __restrict__ gains, int32_t n,
                                                      int32_t* __restrict__ tstep, uint32_t* __restrict__ flag) {
   const int32_t i = blockIdx.x * kBlock + threadIdx.x;
@@ -1550,6 +1560,11 @@ hipError_t launch_run_init(float2* U, float2* gains, int32_t n, int32_t* tstep, 
 
 hipError_t launch_nonfinite_check(const float2* Y, int32_t n, uint32_t* flag, hipStream_t s) {
   hipLaunchKernelGGL(k_nonfinite, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, Y, n, flag);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_nonfinite_check(const BatchPlan& bp, uint32_t* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_batch_nonfinite, dim3(bp.n_row_blocks), dim3(kUpdateRows), 0, s, bp.descs, bp.row_blocks, flag);
   return hipGetLastError();
 }
 

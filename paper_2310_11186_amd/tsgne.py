@@ -597,7 +597,7 @@ def tsgne_kl_noalloc(g: Graph, Y, out, stream=None):
 
 def tsgne_batch_run(graphs, Ys, n_iter, params: tsgne_params, stream=None) -> None:
     """Advances graphs[k] (Graph) on layouts Ys[k] (float32[n_k, 2] device) by
-    n_iter[k] steps together (one captured step replayed for the batch)."""
+    n_iter[k] steps together (one set of launches per step for the batch)."""
     import torch
     count = len(graphs)
     if len(Ys) != count or len(n_iter) != count:
