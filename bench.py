@@ -14,7 +14,7 @@ Prints one JSON line (rank 0).  Also reports the roofline of the dominant
 kernel (the repulsion, timed with HIP events on its own stream; the layouts
 of the timed region run with phase timing on, so each step's launches are
 issued one by one between events; for layouts under 2 s, the time of a
-layout without phase timing, whose steps replay captured chunks, is reported
+layout without phase timing, whose steps are two launches each, is reported
 beside it as layout_ms_replayed), the FP64 oracle timed on the host cores
 over a bounded sample, and, for the default workload, a compact serving leg
 (48 requests of 1K-200K nodes, 500 iterations each: saturated and Poisson
@@ -37,7 +37,10 @@ if ROOT not in sys.path:
 
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X published FP32 vector peak (packed FMA)
 FLOP_PER_PAIR = 13                # algorithmic flops per ordered pair of the repulsion
-FP32_NONPACKED_FMA_TFLOPS = 78.6  # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz (packed FP32 disabled)
+# Packed FP32 is disabled.  A SIMD with eight waves of independent non-packed
+# FP32 FMAs issues one every 2.4 cycles (measured; two waves' side by side):
+# 256 CUs x 4 SIMDs x 64 lanes / 2.4 x 2 flop x 2.4 GHz.
+FP32_NONPACKED_FMA_TFLOPS = 131.1
 # FP32 flop the hardware counts per unordered pair in the symmetric repulsion
 # (rocprofv3 SQ_INSTS_VALU_FLOPS_FP32 x 64 lanes / unordered pairs, FMA = 2;
 # 15 rows per lane, the 300K tile; 17.17 with 14 rows)
@@ -109,8 +112,8 @@ def cpu_baseline(gi, n_iter_total: int, exaggeration_iters: int, perplexity: flo
 
 
 def run_batch(args) -> int:
-    """256 independent SBM graphs, 750 iterations each: batched (one captured
-    step replayed, tile chosen by the autotuner) against one graph at a time
+    """256 independent SBM graphs, 750 iterations each: batched (one set of
+    launches a step, tile chosen by the autotuner) against one graph at a time
     (tsgne_run with each graph's default plan), on the same GPU."""
     import numpy as np
     import torch
@@ -866,8 +869,8 @@ def main() -> int:
     elapsed = time.perf_counter() - t0
 
     # The timed layouts launch each step's kernels one by one between events
-    # (phase timing); a layout without timing replays captured chunks of
-    # steps.  For layouts short enough that launches matter, time that too.
+    # (phase timing); a layout without timing takes two fused launches a
+    # step.  For layouts short enough that launches matter, time that too.
     replayed_ms = None
     if elapsed / args.steps < 2.0:
         reps = 5
@@ -877,7 +880,7 @@ def main() -> int:
             one_step()
         torch.cuda.synchronize()
         replayed_ms = (time.perf_counter() - t1) / reps * 1e3
-        log("layout without phase timing (captured replay): %.2f ms" % replayed_ms)
+        log("layout without phase timing (two launches a step): %.2f ms" % replayed_ms)
 
     n = gi.n
     pairs_per_iter = n * (n - 1)

@@ -455,8 +455,9 @@ tsgne_status run_impl(tsgne_graph* g, float* Y, int32_t n_iter, const tsgne_para
             "initialise run state");
   const float eta = effective_eta(g, p);
   // Two launches per step keep the GPU ahead of the host: issued one by one, 512
-  // steps take 11.3 us each at 2,000 nodes against 11.6 from a captured graph,
-  // whose capture and instantiation cost 0.3 ms a run besides.
+  // steps took 11.3 us each at 2,000 nodes against 11.6 from a captured graph,
+  // whose capture and instantiation cost 0.3 ms a run besides (9.9 us since the
+  // update's loads go out together).
   for (int32_t t = 0; t < n_iter; ++t) {
     const bool sample = trace && t % p->kl_every == 0;
     if (tsgne_status st = enqueue_run_step(g, Y, U, G, p, eta, sample ? trace : nullptr, s)) return st;

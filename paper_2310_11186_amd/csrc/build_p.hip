@@ -151,8 +151,10 @@ __global__ __launch_bounds__(kBlock) void k_row_of(const int32_t* __restrict__ r
 // searches it, and fills in both positions.  Searched entries that are found
 // have distinct reverse entries, none of them searched, so when there are as
 // many searched as others the pattern is symmetric: check's counters take the
-// difference.  Searching for every entry took 67 us at 300,000 nodes and 2.0 M
-// entries (hubs' rows are the ones met most), this 36 us.
+// difference.  At 300,000 nodes and 2.0 M entries a search for every entry
+// (hubs' rows are the ones met most) took 67 us, this 36 where only the check
+// is wanted and 66 with the positions, half of them scattered writes; a search
+// for every entry with its loads together 83.
 __global__ __launch_bounds__(kBlock) void k_mirror(const int32_t* __restrict__ row_ptr,
                                                    const int32_t* __restrict__ col, int32_t n, int64_t nnz,
                                                    int32_t* __restrict__ mirror, const int32_t* __restrict__ row_of,

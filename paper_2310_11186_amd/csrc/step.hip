@@ -1129,8 +1129,8 @@ __global__ __launch_bounds__(kBlock) void k_update(UpdateView v, int32_t T, floa
 // order, partial buffers and reduction order, so a graph advanced inside a
 // batch computes exactly what it computes alone with the same tile size.  Each
 // graph's step index lives in device memory (advanced by the last kernel of a
-// step), so a captured step can be replayed and graphs at different progress
-// can share a launch; graphs with t >= n_iter are skipped.
+// step), so a step's launches are the same every time and graphs at different
+// progress can share one; graphs with t >= n_iter are skipped.
 // ---------------------------------------------------------------------------
 
 // A graph's step index is kept twice, so that no launch reads what it writes:
@@ -1323,10 +1323,12 @@ RepulsionPlan make_plan(int32_t n, int32_t R, int32_t variant) {
   // Small graphs have too few tiles of 4 or more rows to fill the chip: a
   // layout step is then set by one tile's latency, and smaller tiles win in
   // spite of their lower per-pair efficiency.  Crossovers measured on MI355X
-  // over whole layout steps (repulsion, Z sum, update): 1 row per lane up to
-  // about 3,500 nodes (2,000 nodes: 17.7 ms for P and 300 steps against 27.8 ms with
-  // 4 rows), 2 rows up to about 11,000 (5,000 nodes: 24.3 against 31.0 ms),
-  // and from about 11,000 nodes on the cost model below.
+  // over whole layout steps: 1 row per lane up to about 3,500 nodes (a step of
+  // 2,000 nodes takes 12.4 us with 1 row, 12.9 with 2, 16.3 with 4; of 3,500
+  // 12.2, 13.1 and 16.4), 2 rows up to about 11,000 (5,000 nodes: 16.8 us with
+  // 1 row, 15.3 with 2, 16.4 with 4; at 9,001 2 and 4 rows are within 4 %,
+  // 23.6 and 22.8, at 11,500 32.6 and 31.0), and from about 11,000 nodes on
+  // the cost model below.
   if (!tile_rows_supported(R) && p.variant == TSGNE_REPULSION_SYMMETRIC) {
     if (n <= kOneRowMaxNodes) R = 1;
     else if (n <= kTwoRowMaxNodes) R = 2;
@@ -1335,9 +1337,13 @@ RepulsionPlan make_plan(int32_t n, int32_t R, int32_t variant) {
     // Cost model: the tiles (one wave each) of the busiest SIMD, i.e. the
     // tile count over the chip's 1024 SIMDs rounded up, times the tile area,
     // divided by the per-pair efficiency of that tile relative to R = 16
-    // (measured on MI355X as tile-pair slots per second of the repulsion at
-    // 200K-500K nodes, where every SIMD holds 19 or more tiles: 1.004 for
-    // R = 15, 0.996 for 14, 0.997 for 12, 0.969 for 8, 0.827 for 4).  A SIMD
+    // (tile-pair slots per second of the repulsion at 200K-500K nodes, where
+    // every SIMD holds 19 or more tiles, measured before the reciprocals were
+    // grouped: 1.004 for R = 15, 0.996 for 14, 0.997 for 12, 0.969 for 8, 0.827
+    // for 4; now 0.93 for 4, 0.99 for 8, 1.01 to 1.03 for 12 to 15, with which
+    // the picks stay within 3 % of the best as they are: a step of 20,000 nodes
+    // takes 67.6 us against 67.5, of 60,000 453 against 449, of 300,000 9.84 ms
+    // against 9.88 with 16 rows and 9.98 with 14).  A SIMD
     // needs about 64 / R resident tiles (64 independent pairs per step over
     // its waves) to hide the dependent-issue latency, so fewer tiles than that
     // take as long as that many.  Small graphs get small tiles (every SIMD
