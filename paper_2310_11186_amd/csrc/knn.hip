@@ -241,6 +241,24 @@ void launch_overlap(const int32_t* out, const int32_t* count, const int32_t* in_
                      0, s, out, count, in_ptr, source, n, k, before, both, size);
 }
 
+// Stable sort of the pairs by their target's low `bits` bits.  rocPRIM takes 8
+// bits a pass over the pairs; where that leaves a third pass for one or two
+// bits (n from 2^16 to 2^18), 9 bits a pass do in two: 9.0 M pairs of 100,000
+// nodes 281 -> 177 us, a call with 1.05 M pairs 350 -> 308 us.  Up to 2^20 pairs
+// it merges instead, which other settings only slow down (70,000 nodes, k =
+// 10: 357 -> 375 us).
+using NineBitPasses = rocprim::radix_sort_config<
+    rocprim::default_config, rocprim::default_config,
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 12>, rocprim::kernel_config<512, 12>, 9,
+                                         rocprim::block_radix_rank_algorithm::match>>;
+
+hipError_t sort_pairs(void* temp, size_t& bytes, uint32_t* t0, uint32_t* t1, int32_t* s0, int32_t* s1, size_t count,
+                      int bits, hipStream_t s) {
+  if ((bits == 17 || bits == 18) && count > ((size_t)1 << 20))
+    return rocprim::radix_sort_pairs<NineBitPasses>(temp, bytes, t0, t1, s0, s1, count, 0, bits, s);
+  return rocprim::radix_sort_pairs(temp, bytes, t0, t1, s0, s1, count, 0, bits, s);
+}
+
 unsigned blocks_for(int64_t work) { return (unsigned)((work + kBlock - 1) / kBlock); }
 
 }  // namespace
@@ -290,8 +308,7 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   int bits = 1;  // targets 0 .. n
   while (((int64_t)1 << bits) <= n) ++bits;
   size_t sort_bytes = 0, scan_bytes = 0;
-  TSGNE_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, (uint32_t*)nullptr, (uint32_t*)nullptr, (int32_t*)nullptr,
-                                      (int32_t*)nullptr, (size_t)slots, 0, bits, s), "size sort");
+  TSGNE_HIP(sort_pairs(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, (size_t)slots, bits, s), "size sort");
   TSGNE_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, (int32_t*)nullptr, (int32_t*)nullptr, 0, (size_t)n + 1,
                                     rocprim::plus<int32_t>(), s), "size scan");
   // scratch: lists | counts | in_ptr | sizes | pairs before and after the sort
@@ -334,7 +351,7 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   TSGNE_HIP(hipGetLastError(), "launch BFS");
   hipLaunchKernelGGL(k_knn_pairs, dim3(blocks_for(slots)), dim3(kBlock), 0, s, out, count, n, k, t0, s0);
   TSGNE_HIP(hipGetLastError(), "launch pairs");
-  TSGNE_HIP(rocprim::radix_sort_pairs(temp, sort_bytes, t0, t1, s0, s1, (size_t)slots, 0, bits, s), "sort pairs");
+  TSGNE_HIP(sort_pairs(temp, sort_bytes, t0, t1, s0, s1, (size_t)slots, bits, s), "sort pairs");
   hipLaunchKernelGGL(k_knn_in_ptr, dim3(blocks_for((int64_t)n + 1)), dim3(kBlock), 0, s, t1, slots, n, in_ptr);
   TSGNE_HIP(hipGetLastError(), "launch transpose");
   switch ((k + kWave - 1) / kWave) {

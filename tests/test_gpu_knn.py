@@ -86,3 +86,14 @@ def test_knn_graph_at_register_edges(gpu, k):
     orp, ocol = oracle.knn_graph(rp, col, k)
     assert np.array_equal(krp.cpu().numpy(), orp)
     assert np.array_equal(kcol.cpu().numpy(), ocol)
+
+
+@pytest.mark.parametrize("n,k", [(65535, 17), (65536, 17), (131071, 9), (131072, 9), (262143, 5), (262144, 5)])
+def test_knn_graph_at_sort_widths(gpu, n, k):
+    """Targets of 16 to 19 bits, and more pairs than a merge sort takes."""
+    gi = synth.small_dcsbm(n, 3 * n, 2.4, 30, 4, 7)
+    rp, col, d_rp, d_col = device_csr(gi, gpu)
+    krp, kcol = tsgne.tsgne_knn_graph(d_rp, d_col, k)
+    orp, ocol = oracle.knn_graph(rp, col, k)
+    assert np.array_equal(krp.cpu().numpy(), orp)
+    assert np.array_equal(kcol.cpu().numpy(), ocol)
