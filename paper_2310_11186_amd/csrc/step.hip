@@ -639,10 +639,17 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
   }
 }
 
+// Workgroups of a plan's tiles: symmetric ones as in wave_tile_blocks, direct
+// ones a wave each whatever their rows.
+int64_t plan_blocks(const RepulsionPlan& p) {
+  if (p.variant != TSGNE_REPULSION_SYMMETRIC) return (p.items + kWavesPerBlock - 1) / kWavesPerBlock;
+  return wave_tile_blocks(p.items, p.diag, p.R) + p.diag;
+}
+
 template <int R>
 hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag, R) + p.diag));
+  const dim3 grid((unsigned)plan_blocks(p));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
@@ -663,7 +670,7 @@ hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int p
 template <int R>
 hipError_t launch_repulsion_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)(wave_tile_blocks(p.items, p.diag, R) + p.diag));
+  const dim3 grid((unsigned)plan_blocks(p));
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
