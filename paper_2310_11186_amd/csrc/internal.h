@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -217,6 +218,23 @@ struct BlockLayout {
 template <typename T>
 void at_offset(T** p, void* block, size_t offset) {
   *p = reinterpret_cast<T*>(static_cast<char*>(block) + offset);
+}
+
+// A grid of `blocks` workgroups of `threads`, in two dimensions where one would
+// hold 2^32 work-items or more: that is a launch dimension's limit, past which a
+// grid wraps without an error.  Up to gridDim.y - 1 workgroups (of any index
+// from `blocks` on) are more than asked for and must find no work.
+inline dim3 folded_grid(int64_t blocks, int threads) {
+  const int64_t most = ((int64_t)1 << 32) / threads - 1;
+  const int64_t y = std::max<int64_t>(1, (blocks + most - 1) / most);
+  return dim3((unsigned)((blocks + y - 1) / y), (unsigned)y);
+}
+// A workgroup's index in it, in the order of dispatch.  gridDim.x is one more
+// load, so only the second dimension's workgroups read it.
+__device__ __forceinline__ uint32_t folded_block() {
+  uint32_t i = blockIdx.x;
+  if (blockIdx.y != 0) i += blockIdx.y * gridDim.x;
+  return i;
 }
 
 template <typename T>

@@ -578,25 +578,27 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_repulse(cons
                                                     float* __restrict__ zpart32) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
+  const int64_t block = folded_block();
   if (SYM) {
     __shared__ TileLds<R> lds;
     __shared__ double s_z[kWavesPerBlock];
     const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag, R);
-    if ((int64_t)blockIdx.x >= wave_blocks) {
-      const int64_t item = (int64_t)blockIdx.x - wave_blocks;
+    if (block >= wave_blocks) {
+      const int64_t item = block - wave_blocks;
+      if (item >= n_diag) return;
       const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
       tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
       return;
     }
     off_diagonal_tiles<R, SPLIT, true>(
-        blockIdx.x, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+        block, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
           const int2 ab = items[n_diag + k];
           *v = TileView{Y, part, zpart, zpart32, n_diag + k, n, nb, __builtin_amdgcn_readfirstlane(ab.x),
                         __builtin_amdgcn_readfirstlane(ab.y)};
           return true;
         });
   } else {
-    const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    const int64_t item = block * kWavesPerBlock + wave;
     if (item >= n_items) return;
     const int2 ab = items[item];
     const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
@@ -613,25 +615,27 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_zonly(const 
                                                     float* __restrict__ zpart32) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
+  const int64_t block = folded_block();
   if (SYM) {
     __shared__ TileLds<R> lds;
     __shared__ double s_z[kWavesPerBlock];
     const int64_t wave_blocks = wave_tile_blocks(n_items, n_diag, R);
-    if ((int64_t)blockIdx.x >= wave_blocks) {
-      const int64_t item = (int64_t)blockIdx.x - wave_blocks;
+    if (block >= wave_blocks) {
+      const int64_t item = block - wave_blocks;
+      if (item >= n_diag) return;
       const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
       tile_diag<R, SPLIT, false>(Y, n, nb, a, nullptr, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
       return;
     }
     off_diagonal_tiles<R, SPLIT, false>(
-        blockIdx.x, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
+        block, n_items - n_diag, wave, lane, lds, [&](int64_t k, TileView* v) {
           const int2 ab = items[n_diag + k];
           *v = TileView{Y, nullptr, zpart, zpart32, n_diag + k, n, nb, __builtin_amdgcn_readfirstlane(ab.x),
                         __builtin_amdgcn_readfirstlane(ab.y)};
           return true;
         });
   } else {
-    const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    const int64_t item = block * kWavesPerBlock + wave;
     if (item >= n_items) return;
     const int2 ab = items[item];
     const int32_t a = __builtin_amdgcn_readfirstlane(ab.x), b = __builtin_amdgcn_readfirstlane(ab.y);
@@ -649,7 +653,7 @@ int64_t plan_blocks(const RepulsionPlan& p) {
 template <int R>
 hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)plan_blocks(p));
+  const dim3 grid = folded_grid(plan_blocks(p), kBlock);
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
@@ -670,7 +674,7 @@ hipError_t launch_zonly_r(const Workspace& ws, int32_t n, const float2* Y, int p
 template <int R>
 hipError_t launch_repulsion_r(const Workspace& ws, int32_t n, const float2* Y, int precision, hipStream_t s) {
   const RepulsionPlan& p = ws.plan;
-  const dim3 grid((unsigned)plan_blocks(p));
+  const dim3 grid = folded_grid(plan_blocks(p), kBlock);
   const bool split = precision != TSGNE_PREC_FP32;
   const bool sym = p.variant == TSGNE_REPULSION_SYMMETRIC;
   if (split && sym)
@@ -869,15 +873,15 @@ AttractBlocks mix_attract(int64_t tile_blocks, int64_t light, int64_t heavy) {
   return m;
 }
 
-unsigned mixed_grid(int64_t tile_blocks, const AttractBlocks& m) {
-  return (unsigned)(tile_blocks + (int64_t)m.groups * kXcds);
+dim3 mixed_grid(int64_t tile_blocks, const AttractBlocks& m) {
+  return folded_grid(tile_blocks + (int64_t)m.groups * kXcds, kBlock);
 }
 
 // Which workgroup of the launch this is: >= 0 its index among the
 // attraction's (which may lie past its last one), otherwise -1 - its index
 // among the tiles'.
 __device__ __forceinline__ int64_t mixed_block(const AttractBlocks& m) {
-  const uint32_t i = blockIdx.x, group = i / kXcds, q = group / m.stride;
+  const uint32_t i = folded_block(), group = i / kXcds, q = group / m.stride;
   if (q < m.groups && group - q * m.stride == m.stride - 1) return (int64_t)q * kXcds + i % kXcds;
   return -1 - (int64_t)(i - min(q, m.groups) * kXcds);
 }
@@ -898,7 +902,7 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_forces(
   __shared__ double s_z[kWavesPerBlock];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & (kWave - 1);
-  if (tstep && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (tstep && folded_block() == 0 && threadIdx.x == 0) {
     const int32_t t = tstep[0];
     tstep[1] = t;
     tstep[0] = t + 1;
@@ -920,6 +924,7 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_forces(
   const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag, R);
   if (block >= wave_blocks) {
     const int64_t item = block - wave_blocks;
+    if (item >= n_diag) return;
     const int32_t a = __builtin_amdgcn_readfirstlane(items[item].x);
     tile_diag<R, SPLIT>(Y, n, nb, a, part, zpart, zpart32, item, wave, lane, lds.cols[wave], s_z);
     return;
@@ -1178,6 +1183,7 @@ __global__ __launch_bounds__(kBlock, repulse_min_waves<R>()) void k_batch_forces
   }
   const int64_t block = -1 - mixed, wave_blocks = wave_tile_blocks(n_items, n_diag, R);
   if (block >= wave_blocks) {
+    if (block - wave_blocks >= n_diag) return;
     const int4 it = items[block - wave_blocks];
     const BatchDesc& d = descs[__builtin_amdgcn_readfirstlane(it.x)];
     const int32_t a = __builtin_amdgcn_readfirstlane(it.y);
@@ -1443,7 +1449,7 @@ hipError_t launch_forces_r(const tsgne_graph* g, const float2* Y, bool split, in
   const int64_t tiles = wave_tile_blocks(p.items, p.diag, R) + p.diag;
   const AttractBlocks mix = mix_attract(tiles, blocks_for((int64_t)g->n * kRowLanes, kBlock),
                                         blocks_for(g->n_heavy, kWavesPerBlock));
-  const dim3 grid(mixed_grid(tiles, mix));
+  const dim3 grid = mixed_grid(tiles, mix);
   if (split)
     hipLaunchKernelGGL((k_forces<R, true>), grid, dim3(kBlock), 0, s, Y, g->n, p.nb, ws.items, p.items, p.diag,
                        ws.part, ws.zpart, ws.zpart32, g->row_ptr, g->col, g->P, g->heavy, g->n_heavy, ws.attract, mix,
@@ -1519,7 +1525,7 @@ template <int R>
 hipError_t launch_batch_forces_r(const BatchPlan& bp, bool split, hipStream_t s) {
   const int64_t tiles = wave_tile_blocks(bp.n_items, bp.n_diag, R) + bp.n_diag;
   const AttractBlocks mix = mix_attract(tiles, bp.n_light_chunks, blocks_for(bp.n_heavy, kWavesPerBlock));
-  const dim3 grid(mixed_grid(tiles, mix));
+  const dim3 grid = mixed_grid(tiles, mix);
   if (split)
     hipLaunchKernelGGL((k_batch_forces<R, true>), grid, dim3(kBlock), 0, s, bp.descs, bp.items, bp.n_items, bp.n_diag,
                        bp.light_chunks, bp.heavy, bp.n_heavy, mix);

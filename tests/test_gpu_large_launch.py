@@ -62,3 +62,26 @@ def test_direct_tiles_of_four_rows(path_layout):
     _, Z16 = gradient(g, dY, rows, tile_rows=16)
     fz, Z = gradient(g, dY, rows, tile_rows=4, repulsion=tsgne.TSGNE_REPULSION_DIRECT)
     check_repulsion(fz, Z, Z16, Y, rows)
+
+
+@pytest.mark.parametrize("rows_per_lane,n", [(2, 1_060_000), (4, 1_500_000)])
+def test_symmetric_tiles_shared_by_waves(path_layout, gpu, rows_per_lane, n):
+    # more than 2^24 workgroups of two tiles of 128 rows, of one of 256
+    import torch
+    g, dY, Y = path_layout(n)
+    rows = sample_rows(n, 200, 2)
+    _, Z16 = gradient(g, dY, rows, tile_rows=16)
+    kl16 = tsgne.tsgne_kl(g, dY)
+    fz, Z = gradient(g, dY, rows, tile_rows=rows_per_lane)                 # tiles and attraction together
+    check_repulsion(fz, Z, Z16, Y, rows)
+    g.set_timing(True)
+    grad2, Z2 = tsgne.tsgne_gradient(g, dY, 0.0, tsgne.tsgne_params_default(tile_rows=rows_per_lane))
+    g.set_timing(False)                                                    # a launch per phase
+    assert Z2.item() == Z and np.array_equal(-Z * grad2.cpu().numpy()[rows].astype(np.float64), fz)
+    assert abs(tsgne.tsgne_kl(g, dY) - kl16) <= 2 * Z_TOL                  # Z alone
+    if rows_per_lane == 2:                                                 # the batch's launch, against a run's
+        p = tsgne.tsgne_params_default(tile_rows=2, learning_rate=1.0)
+        a, b = dY.clone(), dY.clone()
+        tsgne.tsgne_run(g, a, 1, p)
+        tsgne.tsgne_batch_run([g], [b], [1], p)
+        assert not torch.equal(a, dY) and torch.equal(a, b)
