@@ -400,15 +400,16 @@ __global__ __launch_bounds__(kBlock) void k_calibrate(const int32_t* __restrict_
                                                       const int32_t* __restrict__ heavy, int32_t n_heavy,
                                                       int32_t heavy_blocks, const double* __restrict__ D, double perp,
                                                       double* __restrict__ pcond, double* __restrict__ beta) {
-  if ((int32_t)blockIdx.x < heavy_blocks) {
-    const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6)));
+  const int64_t block = folded_block();
+  if (block < heavy_blocks) {
+    const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(block * (kBlock / kWave) + (threadIdx.x >> 6)));
     if (w >= n_heavy) return;
     const int32_t i = heavy[w];
     const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
     calibrate_row<kWave>(D + b, deg, perp, pcond + b, beta + i, (int)(threadIdx.x & (kWave - 1)));
     return;
   }
-  const int64_t i = ((int64_t)(blockIdx.x - heavy_blocks) * kBlock + threadIdx.x) / kCalLanes;
+  const int64_t i = ((block - heavy_blocks) * kBlock + threadIdx.x) / kCalLanes;
   if (i >= n) return;  // whole groups
   const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
   if (deg > kHeavyDegree) return;
@@ -463,8 +464,8 @@ hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, const int32_
 hipError_t launch_calibrate(const int32_t* row_ptr, int32_t n, const int32_t* heavy, int32_t n_heavy, const double* D,
                             double perplexity, double* pcond, double* beta, hipStream_t s) {
   const int32_t heavy_blocks = (n_heavy + kBlock / kWave - 1) / (kBlock / kWave);
-  hipLaunchKernelGGL(k_calibrate, dim3(heavy_blocks + blocks_for((int64_t)n * kCalLanes)), dim3(kBlock), 0, s, row_ptr,
-                     n, heavy, n_heavy, heavy_blocks, D, perplexity, pcond, beta);
+  hipLaunchKernelGGL(k_calibrate, folded_grid(heavy_blocks + (int64_t)blocks_for((int64_t)n * kCalLanes), kBlock),
+                     dim3(kBlock), 0, s, row_ptr, n, heavy, n_heavy, heavy_blocks, D, perplexity, pcond, beta);
   return hipGetLastError();
 }
 

@@ -1,10 +1,11 @@
 """Launches at sizes where a launch dimension's 2^32 work-items are the limit:
-a tile list of more than 2^24 tiles, whose last rows and normaliser have to be
-there like the first ones'."""
+tile lists of more than 2^24 tiles and arrays of 2^28 and more nodes, whose last
+rows have to be there like the first ones'."""
 import numpy as np
 import pytest
 
-from bars import Z_TOL, sample_rows
+import oracle
+from bars import P_TOL, Z_TOL, rel_l2, sample_rows
 from paper_2310_11186_amd import tsgne
 
 pytestmark = pytest.mark.gpu
@@ -85,3 +86,26 @@ def test_symmetric_tiles_shared_by_waves(path_layout, gpu, rows_per_lane, n):
         tsgne.tsgne_run(g, a, 1, p)
         tsgne.tsgne_batch_run([g], [b], [1], p)
         assert not torch.equal(a, dY) and torch.equal(a, b)
+
+
+def late_graph(n, edges, gpu):
+    """CSR on the device of n nodes, of which the last 64 have the edges (numbered from the first of them)."""
+    import torch
+    rp, col = tsgne.tsgne_csr_from_edges(64, np.asarray(edges, np.int32))
+    row_ptr = torch.zeros(n + 1, dtype=torch.int32, device=gpu)
+    row_ptr[n - 64:] = torch.from_numpy(rp).to(gpu)
+    return row_ptr, torch.from_numpy(col + (n - 64)).to(gpu), rp, col
+
+
+def test_calibration_of_2_28_nodes(gpu):
+    import torch
+    n = 2 ** 28 + 100                                       # sixteen lanes each
+    row_ptr, dcol, rp, col = late_graph(n, [(i, j) for i in range(0, 60, 2) for j in range(i + 1, 64, 3)], gpu)
+    X = torch.zeros((n, 1), dtype=torch.float32, device=gpu)
+    x = np.random.default_rng(28).standard_normal((64, 1)).astype(np.float32)
+    X[n - 64:] = torch.from_numpy(x).to(gpu)
+    g = tsgne.tsgne_build_P(row_ptr, dcol, X, 5.0)
+    P = np.zeros(col.shape[0], np.float32)
+    assert tsgne.lib().tsgne_graph_export(g.handle, None, None, None, P.ctypes.data, None) == tsgne.TSGNE_OK
+    g.close()
+    assert rel_l2(P, oracle.build_P(rp, col, x, 5.0)[0]) <= P_TOL
