@@ -194,7 +194,8 @@ __global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict
   unsigned long long* s_sum = reinterpret_cast<unsigned long long*>(s_c + k);
   int32_t* s_cnt = reinterpret_cast<int32_t*>(s_sum + 2 * k);
   const int sub = threadIdx.x & (kPointLanes - 1);
-  const int64_t i = (int64_t)blockIdx.x * kPassPoints + threadIdx.x / kPointLanes;
+  const int64_t block = folded_block();
+  const int64_t i = block * kPassPoints + threadIdx.x / kPointLanes;
   const int2 pt = i < n ? q[i] : make_int2(0, 0);
   const int32_t old = i < n ? labels[i] : 0;
   const int c = threadIdx.x;  // this thread's centre, if there are so many
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(kPassThreads) void k_km_pass(const int2* __restrict
     m = st.centre_in[c];
   }
   const int32_t before = *st.moved_before;
-  const bool keeper = blockIdx.x == 0;  // the workgroup that writes the state
+  const bool keeper = block == 0;  // the workgroup that writes the state
   if (keeper && threadIdx.x == 0) *st.moved_next = 0;
   if (st.p > 1 && before == 0) {  // converged (uniform)
     if (keeper && threadIdx.x == 0 && st.done[0] == 0) {
@@ -488,14 +489,14 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
 
   int32_t host_done[2] = {0, 0};
   int32_t pass = 0, chunk = kIterChunk;
-  const unsigned pass_blocks = (unsigned)(((int64_t)n + kPassPoints - 1) / kPassPoints);
+  const dim3 pass_grid = folded_grid(((int64_t)n + kPassPoints - 1) / kPassPoints, kPassThreads);
   while (pass < max_iter) {
     // a pass after convergence returns at once: later chunks are longer, as a
     // check costs more than a few of those
     const int32_t last = (int32_t)std::min<int64_t>(max_iter, (int64_t)pass + chunk);
     chunk = std::min(2 * chunk, kMaxIterChunk);
     for (int32_t it = pass + 1; it <= last; ++it)
-      hipLaunchKernelGGL(k_km_pass, dim3(pass_blocks), dim3(kPassThreads), km_lds_bytes(k), s, q, n, k, labels_d,
+      hipLaunchKernelGGL(k_km_pass, pass_grid, dim3(kPassThreads), km_lds_bytes(k), s, q, n, k, labels_d,
                          km_pass(st, it));
     TSGNE_HIP(hipGetLastError(), "launch k-means passes");
     TSGNE_HIP(hipMemcpyAsync(host_done, done, sizeof(host_done), hipMemcpyDeviceToHost, s), "read convergence");

@@ -109,3 +109,15 @@ def test_calibration_of_2_28_nodes(gpu):
     assert tsgne.lib().tsgne_graph_export(g.handle, None, None, None, P.ctypes.data, None) == tsgne.TSGNE_OK
     g.close()
     assert rel_l2(P, oracle.build_P(rp, col, x, 5.0)[0]) <= P_TOL
+
+
+def test_kmeans_of_2_30_points(gpu):
+    import torch
+    n = 2 ** 30 + 300                                       # four lanes each
+    h = n // 2
+    Y = torch.zeros((n, 2), dtype=torch.float32, device=gpu)
+    Y[h:] = 1.0
+    labels, passes = tsgne.tsgne_kmeans(Y, torch.tensor([0, n - 1], dtype=torch.int32, device=gpu), 5)
+    assert passes == 2 and not labels[:h].any() and bool((labels[h:] == 1).all())
+    del Y, labels
+    torch.cuda.empty_cache()
