@@ -442,18 +442,19 @@ __global__ __launch_bounds__(kBlock) void k_sp_decode(int32_t n, int32_t d, uint
   extern __shared__ uint32_t s_word[];  // [1 + n_planes][kDecodeNodes * W]: vis, then the planes
   constexpr int kWords = kDecodeNodes * W;
   const int tid = threadIdx.x;
-  const int32_t v0 = blockIdx.x * kDecodeNodes;
-  const int32_t rows = min(kDecodeNodes, n - v0);
+  const int64_t v0 = (int64_t)folded_block() * kDecodeNodes;
+  if (v0 >= n) return;
+  const int32_t rows = (int32_t)min<int64_t>(kDecodeNodes, n - v0);
   int stop = csr_failed(check) ? 1 : 0;
   if (last_flags && tid < kSlots) stop |= last_flags[tid * kSlotStride];
   for (int32_t q = tid; q < (1 + n_planes) * kWords; q += kBlock) {
     const int32_t k = q / kWords, o = q - k * kWords;
     if (o < rows * W)
-      s_word[q] = k == 0 ? vis[(int64_t)v0 * W + o] : planes[(k - 1) * plane_stride + (int64_t)v0 * W + o];
+      s_word[q] = k == 0 ? vis[v0 * W + o] : planes[(k - 1) * plane_stride + v0 * W + o];
   }
   if (__syncthreads_or(stop)) return;
   const int32_t count = rows * d;
-  float* const out = X + (int64_t)v0 * d;
+  float* const out = X + v0 * d;
   for (int32_t f = 4 * tid; f < count; f += 4 * kBlock) {
     int32_t r = d == 1 ? f : (int32_t)__umulhi((uint32_t)f, recip_d);  // f / d
     int32_t j = f - r * d;
@@ -555,15 +556,15 @@ template <int W>
 hipError_t launch_decode(int32_t n, int32_t d, const uint32_t* vis, const uint32_t* planes, int64_t plane_stride,
                          int n_planes, float beyond, const uint32_t* check, const int32_t* last_flags, float* X,
                          hipStream_t s) {
-  const unsigned blocks = (unsigned)(((int64_t)n + kDecodeNodes - 1) / kDecodeNodes);
+  const dim3 grid = folded_grid(((int64_t)n + kDecodeNodes - 1) / kDecodeNodes, kBlock);
   const size_t lds = sizeof(uint32_t) * (1 + (size_t)n_planes) * kDecodeNodes * W;  // at most 64 KB
   // ceil(2^32 / d): the high word of its product with f is f / d for f up to kDecodeNodes * 256
   const uint32_t recip_d = d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d);
   if (d % 4 == 0)
-    hipLaunchKernelGGL((k_sp_decode<W, true>), dim3(blocks), dim3(kBlock), lds, s, n, d, recip_d, vis, planes,
+    hipLaunchKernelGGL((k_sp_decode<W, true>), grid, dim3(kBlock), lds, s, n, d, recip_d, vis, planes,
                        plane_stride, n_planes, beyond, check, last_flags, X);
   else
-    hipLaunchKernelGGL((k_sp_decode<W, false>), dim3(blocks), dim3(kBlock), lds, s, n, d, recip_d, vis, planes,
+    hipLaunchKernelGGL((k_sp_decode<W, false>), grid, dim3(kBlock), lds, s, n, d, recip_d, vis, planes,
                        plane_stride, n_planes, beyond, check, last_flags, X);
   return hipGetLastError();
 }

@@ -121,3 +121,13 @@ def test_kmeans_of_2_30_points(gpu):
     assert passes == 2 and not labels[:h].any() and bool((labels[h:] == 1).all())
     del Y, labels
     torch.cuda.empty_cache()
+
+
+def test_hop_distances_of_2_30_nodes(gpu):
+    import torch
+    n = 2 ** 30 + 70                                        # decoded by four work-items each
+    row_ptr, col, _, _ = late_graph(n, [(i, i + 1) for i in range(60, 63)], gpu)
+    X, _ = tsgne.tsgne_shortest_path_embedding(row_ptr, col, torch.tensor([n - 1], dtype=torch.int32, device=gpu), 2.0)
+    assert X[n - 4:, 0].tolist() == [3.0, 2.0, 1.0, 0.0] and bool((X[:n - 4] == 3.0).all())
+    del X, row_ptr
+    torch.cuda.empty_cache()
