@@ -138,3 +138,14 @@ def test_sp_rejects(gpu):
         tsgne.tsgne_shortest_path_embedding(d_rp, torch.from_numpy(bad).to(gpu),
                                             torch.tensor([0], dtype=torch.int32, device=gpu))
     assert e.value.status == tsgne.TSGNE_E_GRAPH
+
+
+@pytest.mark.parametrize("far", [11, 12, 13, 23, 24, 25])     # the last level with a new node, around chunks of 12
+@pytest.mark.parametrize("over", [-1.0, 0.0, 0.5, 1e6])       # the threshold, less that level
+def test_sp_searches_that_end_around_a_chunk(gpu, far, over):
+    n = far + 1
+    targets = np.full(9, 0, np.int32)
+    targets[::2] = n - 1
+    X, oX, levels = run_both(gpu, n, path_edges(n), targets, far + over)
+    assert np.array_equal(X, oX)
+    assert levels <= min(np.floor(far + over), n - 1)
