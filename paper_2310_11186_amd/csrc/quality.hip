@@ -20,7 +20,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kFinal = 1024;          // threads of the one-block kernels
 constexpr int kMaxClusters = 1024;    // k-means centres held in LDS
-constexpr int kIterChunk = 8;         // k-means passes queued before the first check
+constexpr int kIterChunk = 8;         // k-means passes that the first check covers
 constexpr int kMaxIterChunk = 32;     // and at most before a later one
 constexpr int kLdsContingency = 4096; // contingency tables up to this size are counted in LDS first
 constexpr uint32_t kErrFinite = 1u, kErrSeed = 2u, kErrLabel = 4u;
@@ -491,9 +491,12 @@ tsgne_status tsgne_kmeans(int32_t n, const float* Y_d, int32_t k, const int32_t*
   int32_t pass = 0, chunk = kIterChunk;
   const dim3 pass_grid = folded_grid(((int64_t)n + kPassPoints - 1) / kPassPoints, kPassThreads);
   while (pass < max_iter) {
-    // a pass after convergence returns at once: later chunks are longer, as a
-    // check costs more than a few of those
-    const int32_t last = (int32_t)std::min<int64_t>(max_iter, (int64_t)pass + chunk);
+    // A pass after convergence returns at once: later chunks are longer, as a
+    // check costs more than a few of those.  It is the pass after the last one
+    // that finds convergence, so the first chunk holds one more: 100 points in 5
+    // clusters, which take 8 passes, waited for a second chunk without it (224 us,
+    // now 125).
+    const int32_t last = (int32_t)std::min<int64_t>(max_iter, (int64_t)pass + chunk + (pass == 0 ? 1 : 0));
     chunk = std::min(2 * chunk, kMaxIterChunk);
     for (int32_t it = pass + 1; it <= last; ++it)
       hipLaunchKernelGGL(k_km_pass, pass_grid, dim3(kPassThreads), km_lds_bytes(k), s, q, n, k, labels_d,

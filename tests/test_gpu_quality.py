@@ -122,3 +122,24 @@ def test_kmeans_at_group_edges(gpu, n, k):
     ol, oit = oracle.kmeans(Y, seeds)
     assert iters == oit
     assert np.array_equal(labels.cpu().numpy(), ol)
+
+
+def cloud_needing(passes):
+    """Points and five seeds for which k-means makes so many passes, the last without a change."""
+    for seed in range(500):
+        Y = np.random.default_rng(seed).standard_normal((600, 2)).astype(np.float32)
+        seeds = np.arange(5, dtype=np.int32)
+        labels, it = oracle.kmeans(Y, seeds, 100)
+        if it == passes:
+            return Y, seeds, labels
+
+
+@pytest.mark.parametrize("passes", [7, 8, 9, 10, 24, 25, 26])    # around the passes queued before a check
+def test_kmeans_converging_around_a_check(gpu, passes):
+    import torch
+    Y, seeds, ol = cloud_needing(passes)
+    dY, ds = torch.from_numpy(Y).to(gpu), torch.from_numpy(seeds).to(gpu)
+    for max_iter in (passes - 1, passes, passes + 1, 100):
+        labels, it = tsgne.tsgne_kmeans(dY, ds, max_iter)
+        assert it == min(passes, max_iter)
+        assert np.array_equal(labels.cpu().numpy(), ol if max_iter >= passes else oracle.kmeans(Y, seeds, max_iter)[0])
