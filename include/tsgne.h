@@ -133,7 +133,8 @@ TSGNE_API tsgne_status tsgne_csr_from_edges(int32_t n, int64_t m, const int32_t*
  *   knn_col_d                -- int32[knn_capacity] (device, written); 2*n*k
  *                               always suffices
  *   *knn_nnz                 -- number of stored entries of the result (also
- *                               set when the capacity is too small)
+ *                               set when the capacity is too small; the arrays
+ *                               are then left as they were)
  * Synchronising.  Errors: E_INVAL (bad sizes, k, capacity too small),
  * E_GRAPH (input CSR not canonical/symmetric), E_NOMEM, E_DEVICE.
  */

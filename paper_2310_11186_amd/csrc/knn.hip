@@ -205,7 +205,9 @@ __global__ __launch_bounds__(kBlock) void k_knn_overlap(const int32_t* __restric
   }
 }
 
-// Entry t of the lists and pair t of the transpose into their places.
+// Entry t of the lists and pair t of the transpose into their places, and the
+// row pointers to the caller (only now: a call that is refused because col is
+// too small has written neither).
 __global__ __launch_bounds__(kBlock) void k_knn_merge(const int32_t* __restrict__ out,
                                                       const int32_t* __restrict__ count,
                                                       const int32_t* __restrict__ before,
@@ -213,9 +215,12 @@ __global__ __launch_bounds__(kBlock) void k_knn_merge(const int32_t* __restrict_
                                                       const uint32_t* __restrict__ target,
                                                       const int32_t* __restrict__ source,
                                                       const int32_t* __restrict__ in_ptr, int32_t n, int32_t k,
-                                                      const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col) {
+                                                      const int32_t* __restrict__ row_ptr,
+                                                      int32_t* __restrict__ row_ptr_out, int32_t* __restrict__ col) {
   const uint32_t t = blockIdx.x * kBlock + threadIdx.x;  // n * k < 2^30
   if (t >= (uint32_t)n * (uint32_t)k) return;
+  if (t < (uint32_t)n) row_ptr_out[t] = row_ptr[t];
+  if (t == 0) row_ptr_out[n] = row_ptr[n];
   const int32_t i = (int32_t)(t / (uint32_t)k), at = (int32_t)(t - (uint32_t)i * (uint32_t)k);
   if (at < count[i]) col[row_ptr[i] + at + before[t]] = out[t];
   const int32_t j = (int32_t)target[t];
@@ -311,7 +316,7 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   TSGNE_HIP(sort_pairs(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, (size_t)slots, bits, s), "size sort");
   TSGNE_HIP(rocprim::exclusive_scan(nullptr, scan_bytes, (int32_t*)nullptr, (int32_t*)nullptr, 0, (size_t)n + 1,
                                     rocprim::plus<int32_t>(), s), "size scan");
-  // scratch: lists | counts | in_ptr | sizes | pairs before and after the sort
+  // scratch: lists | counts | in_ptr | sizes | row pointers | pairs before and after the sort
   // (the unsorted ones' place is taken by before and both) | rocPRIM's own;
   // the CSR check, which is done before any of them, from the same start.  One
   // allocation: with a second, small one before it the pool now and then gave
@@ -326,6 +331,7 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   const size_t o_count = place(sizeof(int32_t) * (size_t)n);
   const size_t o_in = place(sizeof(int32_t) * ((size_t)n + 1));
   const size_t o_size = place(sizeof(int32_t) * ((size_t)n + 1));
+  const size_t o_ptr = place(sizeof(int32_t) * ((size_t)n + 1));
   const size_t o_t0 = place(sizeof(int32_t) * (size_t)slots);
   const size_t o_s0 = place(sizeof(int32_t) * ((size_t)slots + (size_t)n));
   const size_t o_t1 = place(sizeof(int32_t) * (size_t)slots);
@@ -337,7 +343,7 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
   char* const base = static_cast<char*>(tmp.p);
   if (tsgne_status st = validate_csr_in(n, nnz, row_ptr_d, col_d, base, s)) return st;
   auto ints = [&](size_t at) { return reinterpret_cast<int32_t*>(base + at); };
-  int32_t *out = ints(o_out), *count = ints(o_count), *in_ptr = ints(o_in), *size = ints(o_size);
+  int32_t *out = ints(o_out), *count = ints(o_count), *in_ptr = ints(o_in), *size = ints(o_size), *ptr = ints(o_ptr);
   uint32_t *t0 = reinterpret_cast<uint32_t*>(base + o_t0), *t1 = reinterpret_cast<uint32_t*>(base + o_t1);
   int32_t *s0 = ints(o_s0), *s1 = ints(o_s1), *before = ints(o_t0), *both = ints(o_s0);
   void* const temp = base + o_temp;
@@ -361,15 +367,15 @@ tsgne_status tsgne_knn_graph(int32_t n, int64_t nnz, const int32_t* row_ptr_d, c
     default: launch_overlap<4>(out, count, in_ptr, s1, n, k, before, both, size, s); break;
   }
   TSGNE_HIP(hipGetLastError(), "launch overlap");
-  TSGNE_HIP(rocprim::exclusive_scan(temp, scan_bytes, size, knn_row_ptr_d, 0, (size_t)n + 1, rocprim::plus<int32_t>(),
-                                    s), "scan row sizes");
+  TSGNE_HIP(rocprim::exclusive_scan(temp, scan_bytes, size, ptr, 0, (size_t)n + 1, rocprim::plus<int32_t>(), s),
+            "scan row sizes");
   int32_t total = 0;
-  TSGNE_HIP(hipMemcpyAsync(&total, knn_row_ptr_d + n, sizeof(int32_t), hipMemcpyDeviceToHost, s), "read size");
+  TSGNE_HIP(hipMemcpyAsync(&total, ptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s), "read size");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise row sizes");
   *knn_nnz = total;
   if (total > knn_capacity) return fail(TSGNE_E_INVAL, "knn_col capacity is smaller than the result (see *knn_nnz)");
   hipLaunchKernelGGL(k_knn_merge, dim3(blocks_for(slots)), dim3(kBlock), 0, s, out, count, before, both, t1, s1,
-                     in_ptr, n, k, knn_row_ptr_d, knn_col_d);
+                     in_ptr, n, k, ptr, knn_row_ptr_d, knn_col_d);
   TSGNE_HIP(hipGetLastError(), "launch merge");
   TSGNE_HIP(hipStreamSynchronize(s), "synchronise kNN graph");
   return TSGNE_OK;

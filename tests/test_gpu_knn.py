@@ -97,3 +97,24 @@ def test_knn_graph_at_sort_widths(gpu, n, k):
     orp, ocol = oracle.knn_graph(rp, col, k)
     assert np.array_equal(krp.cpu().numpy(), orp)
     assert np.array_equal(kcol.cpu().numpy(), ocol)
+
+
+@pytest.mark.parametrize("n,k", [(500, 5), (256, 1), (3000, 90)])
+def test_knn_graph_leaves_the_arrays_of_a_refused_call(gpu, n, k):
+    import ctypes
+    import torch
+    gi = synth.small_dcsbm(n, 3 * n, 2.3, 10, 4, 13)
+    rp, col, d_rp, d_col = device_csr(gi, gpu)
+    orp, ocol = oracle.knn_graph(rp, col, k)
+    krp = torch.full((n + 1,), -7, dtype=torch.int32, device=gpu)
+    kcol = torch.full((ocol.shape[0],), -7, dtype=torch.int32, device=gpu)
+    nnz = ctypes.c_int64()
+
+    def call(capacity):
+        return tsgne.lib().tsgne_knn_graph(n, col.shape[0], d_rp.data_ptr(), d_col.data_ptr(), k, krp.data_ptr(),
+                                           kcol.data_ptr(), capacity, ctypes.byref(nnz), None)
+
+    assert call(ocol.shape[0] - 1) == tsgne.TSGNE_E_INVAL and nnz.value == ocol.shape[0]
+    assert bool((krp == -7).all()) and bool((kcol == -7).all())
+    assert call(ocol.shape[0]) == tsgne.TSGNE_OK and nnz.value == ocol.shape[0]
+    assert np.array_equal(krp.cpu().numpy(), orp) and np.array_equal(kcol.cpu().numpy(), ocol)
