@@ -31,6 +31,12 @@
  *    ceil(n / (64 * tile_rows)) (about 0.8 GB at 300K nodes, 31 GB at 2M with
  *    16 rows per lane), plus about 40 bytes per node and 8 per tile; a graph
  *    whose workspace does not fit fails with E_NOMEM.
+ *  - Scratch of single calls (affinities, neighbourhood graph, shortest paths,
+ *    k-means, NMI, AQ, orders, runs) comes from a stream-ordered pool of the
+ *    library's, one per device, which keeps up to 1 GiB of it for the next call
+ *    (the neighbourhood graph of 300,000 nodes with k = 90: 0.8 GB).  The HIP
+ *    runtime takes it back when an allocation of the process needs it; other
+ *    processes do not see it before that.
  */
 #ifndef TSGNE_H
 #define TSGNE_H
