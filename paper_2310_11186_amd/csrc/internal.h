@@ -68,7 +68,7 @@ struct Workspace {
   double* klpart = nullptr;     // [kl_blocks] KL partial sums
   double* klout = nullptr;      // [1]
   int32_t* tstep = nullptr;     // [2] device step counter of a run: next step, step being run
-  double* pinned = nullptr;     // host-pinned scratch for read-backs (allocated by the first)
+  double* pinned = nullptr;     // host-pinned word for read-backs (NULL: none was left)
   int32_t kl_blocks = 0;
 };
 
