@@ -303,6 +303,10 @@ __global__ __launch_bounds__(kBlock) void k_sqdist(const int32_t* __restrict__ r
 // ---------------------------------------------------------------------------
 
 constexpr int kCalLanes = 16;
+// Steps of the search at most.  Squared distances of FP32 coordinates span up
+// to 1e166, 280 steps of a factor of 4; with 200, rows that span 1e121 and more
+// were left short of their beta.  Ordinary rows take 5 to 8.
+constexpr int kCalSteps = 1000;
 
 template <int LANES>
 __device__ __forceinline__ double group_sum(double v) {
@@ -317,11 +321,14 @@ __device__ __forceinline__ double group_min(double v) {
 }
 
 // beta_i = 1/(2 sigma_i^2) such that the row's entropy is log(perp) (section
-// 2.1: sigma_i is found by a search), to a relative 1e-13.  With p_k =
-// exp(-beta delta_k) / S the entropy in nats is H = log(S) + beta <delta>, and
-// dH / d(log beta) = -beta^2 Var(delta): Newton's iteration on log(beta) from
-// 1/mean(delta), inside the bracket that the signs of H - log(perp) give, and
-// doubling, halving or bisecting wherever a step would leave it.
+// 2.1: sigma_i is found by a search).  With p_k = exp(-beta delta_k) / S the
+// entropy in nats is H = log(S) + beta <delta>, and dH / d(log beta) =
+// -beta^2 Var(delta): Newton's iteration on log(beta) from 1/mean(delta), inside
+// the bracket that the signs of H - log(perp) give, and doubling, halving or
+// bisecting wherever a step would leave it.  It ends when the bracket is 1e-13
+// of beta wide or the steps no longer shrink, at the rounding of H: log(beta) is
+// then within that rounding over beta^2 Var(delta) of the root, which is more
+// than 1e-13 where H is flat, that is, where p hardly depends on beta.
 //
 // Bound by the FP64 exponentials.  One thread per row and bisection alone took
 // 1.66 ms at 100,000 nodes (perplexity 30, 45 to 50 evaluations of up to 64
@@ -358,7 +365,7 @@ __device__ void calibrate_row(const double* __restrict__ Dr, int64_t deg, double
   }
   const double target = log(perp);
   double lo = 0.0, hi = INFINITY, bt = 1.0 / mean, last = INFINITY;
-  for (int it = 0; it < 200; ++it) {
+  for (int it = 0; it < kCalSteps; ++it) {
     double S = 0.0, T = 0.0, V = 0.0;
     for (int64_t k = lane; k < deg; k += LANES) {
       const double dk = Dr[k] - dmin;

@@ -68,3 +68,20 @@ def test_distances_at_group_edges(gpu, d, cut):
     P, _ = oracle.build_P(*oracle.csr_from_edges(n, edges), X, 15.0)
     assert rel_l2(g.export()["P"], P) <= P_TOL
     g.close()
+
+
+@pytest.mark.parametrize("perp", [1.5, 3.0, 5.0, 9.0])
+@pytest.mark.parametrize("near,far", [(1e-10, 1e10), (1e-30, 1e38), (2e-38, 1e38)])
+def test_calibration_over_the_range_of_fp32(gpu, near, far, perp):
+    """A hub with eight near and eight far leaves whose beta lies far from 1 / mean."""
+    import torch
+    n = 17
+    edges = np.stack([np.zeros(16, np.int32), np.arange(1, 17, dtype=np.int32)], 1)
+    X = np.concatenate([[0.0], near * np.linspace(1, 2, 8), far * np.linspace(1, 2, 8)]).astype(np.float32)[:, None]
+    rp, col = tsgne.tsgne_csr_from_edges(n, edges)
+    g = tsgne.tsgne_build_P(*(torch.from_numpy(a).to(gpu) for a in (rp, col, X)), perp)
+    ex = g.export()
+    P, beta = oracle.build_P(*oracle.csr_from_edges(n, edges), X, perp)
+    assert rel_l2(ex["P"], P) <= P_TOL
+    assert abs(ex["beta"][0] / beta[0] - 1.0) <= 1e-11
+    g.close()
