@@ -80,9 +80,10 @@ constexpr int kMaxGroups = 8;
 // Group key of the running long request: kHeadKey + its tile rows.
 constexpr int32_t kHeadKey = 1000;
 
-// Shortest time of one step of the smallest graphs (a few dependent kernel
-// launches), below which a step does not get faster however few pairs it has.
-constexpr double kStepFloorSeconds = 15e-6;
+// Shortest time of one step of the smallest graphs (two dependent kernel
+// launches; 9.9 us at 1,000 nodes), below which a step does not get faster however
+// few pairs it has.
+constexpr double kStepFloorSeconds = 10e-6;
 
 // Estimated GPU time of n_iter steps of an n-node graph alone.
 double alone_seconds(int32_t n, int32_t n_iter, double pair_rate) {
@@ -131,8 +132,9 @@ struct tsgne_server {
   bool have_first = false;
   Clock::time_point t_first, t_last_done;
   double busy_s = 0.0, admit_s = 0.0, plan_s = 0.0;
-  // ordered pairs evaluated per second, refined from measured rounds
-  double pair_rate = 5e12;
+  // ordered pairs evaluated per second, refined from measured rounds (300,000
+  // nodes: 9.2e12)
+  double pair_rate = 9e12;
   // the one-at-a-time schedule's clock: the estimated finish of the last
   // request admitted, had every request run alone in submission order
   Clock::time_point fifo_clock;
