@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_keys_csr(const uint64_t* __restrict_
 __global__ __launch_bounds__(kBlock) void k_permute_rows(const uint32_t* __restrict__ src,
                                                          const int32_t* __restrict__ perm, int32_t n, int32_t words,
                                                          int inverse, uint32_t* __restrict__ dst) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t t = (int64_t)folded_block() * kBlock + threadIdx.x;
   if (t >= (int64_t)n * words) return;
   const int32_t r = (int32_t)(t / words), w = (int32_t)(t % words);
   const int32_t p = perm[r];
@@ -296,7 +296,7 @@ tsgne_status tsgne_permute_rows(int32_t n, int32_t row_bytes, const void* src_d,
   if (src_d == dst_d) return fail(TSGNE_E_INVAL, "src and dst must not be the same buffer");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int32_t words = row_bytes / 4;
-  hipLaunchKernelGGL(k_permute_rows, dim3(blocks_for((int64_t)n * words)), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(k_permute_rows, folded_grid(((int64_t)n * words + kBlock - 1) / kBlock, kBlock), dim3(kBlock), 0, s,
                      static_cast<const uint32_t*>(src_d), perm_d, n, words, inverse ? 1 : 0,
                      static_cast<uint32_t*>(dst_d));
   TSGNE_HIP(hipGetLastError(), "launch row permutation");

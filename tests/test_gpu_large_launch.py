@@ -131,3 +131,15 @@ def test_hop_distances_of_2_30_nodes(gpu):
     assert X[n - 4:, 0].tolist() == [3.0, 2.0, 1.0, 0.0] and bool((X[:n - 4] == 3.0).all())
     del X, row_ptr
     torch.cuda.empty_cache()
+
+
+def test_permuted_rows_of_2_32_words(gpu):
+    import torch
+    n, words = 2 ** 20, 4100
+    src = torch.arange(n, dtype=torch.int32, device=gpu)[:, None] + torch.arange(words, dtype=torch.int32, device=gpu)
+    perm = torch.arange(n - 1, -1, -1, dtype=torch.int32, device=gpu)
+    dst = tsgne.tsgne_permute_rows(src, perm)
+    for rows in torch.arange(n, device=gpu).split(2 ** 17):
+        assert torch.equal(dst[rows], src[n - 1 - rows])
+    del src, dst, rows
+    torch.cuda.empty_cache()
