@@ -54,7 +54,8 @@ template <int U>
 __global__ __launch_bounds__(kBlock) void k_knn_bfs(const int32_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ col, int32_t n, int32_t k,
                                                     int32_t* __restrict__ out, int32_t* __restrict__ out_count) {
-  const int32_t i = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
+  // at most 2^30 / k nodes, so a wave's index fits
+  const int32_t i = __builtin_amdgcn_readfirstlane((int32_t)(folded_block() * kWavesPerBlock + (threadIdx.x >> 6)));
   if (i >= n) return;
   const int lane = threadIdx.x & (kWave - 1);
   int32_t hit[U];                          // node found at index lane + 64 u
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(kBlock) void k_knn_overlap(const int32_t* __restric
                                                         const int32_t* __restrict__ source, int32_t n, int32_t k,
                                                         int32_t* __restrict__ before, int32_t* __restrict__ both,
                                                         int32_t* __restrict__ size) {
-  const int32_t j = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
+  const int32_t j = __builtin_amdgcn_readfirstlane((int32_t)(folded_block() * kWavesPerBlock + (threadIdx.x >> 6)));
   if (j > n) return;
   const int lane = threadIdx.x & (kWave - 1);
   if (j == n) {  // one more entry, so that a scan of the sizes ends with their sum
@@ -235,15 +236,15 @@ __global__ __launch_bounds__(kBlock) void k_knn_merge(const int32_t* __restrict_
 template <int U>
 void launch_lists(const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t k, int32_t* out, int32_t* count,
                   hipStream_t s) {
-  hipLaunchKernelGGL(k_knn_bfs<U>, dim3((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0, s,
-                     row_ptr, col, n, k, out, count);
+  hipLaunchKernelGGL(k_knn_bfs<U>, folded_grid(((int64_t)n + kWavesPerBlock - 1) / kWavesPerBlock, kBlock),
+                     dim3(kBlock), 0, s, row_ptr, col, n, k, out, count);
 }
 
 template <int U>
 void launch_overlap(const int32_t* out, const int32_t* count, const int32_t* in_ptr, const int32_t* source, int32_t n,
                     int32_t k, int32_t* before, int32_t* both, int32_t* size, hipStream_t s) {
-  hipLaunchKernelGGL(k_knn_overlap<U>, dim3((unsigned)((n + 1 + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
-                     0, s, out, count, in_ptr, source, n, k, before, both, size);
+  hipLaunchKernelGGL(k_knn_overlap<U>, folded_grid(((int64_t)n + 1 + kWavesPerBlock - 1) / kWavesPerBlock, kBlock),
+                     dim3(kBlock), 0, s, out, count, in_ptr, source, n, k, before, both, size);
 }
 
 // Stable sort of the pairs by their target's low `bits` bits.  rocPRIM takes 8

@@ -143,3 +143,12 @@ def test_permuted_rows_of_2_32_words(gpu):
         assert torch.equal(dst[rows], src[n - 1 - rows])
     del src, dst, rows
     torch.cuda.empty_cache()
+
+
+def test_neighbourhood_graph_of_2_26_nodes(gpu):
+    n = 2 ** 26 + 100                                       # a wave each
+    row_ptr, dcol, rp, col = late_graph(n, [(i, j) for i in range(0, 60, 2) for j in range(i + 1, 64, 3)], gpu)
+    krp, kcol = tsgne.tsgne_knn_graph(row_ptr, dcol, 3)
+    orp, ocol = oracle.knn_graph(rp, col, 3)
+    assert not krp[:n - 64].any()
+    assert np.array_equal(krp[n - 64:].cpu().numpy(), orp) and np.array_equal(kcol.cpu().numpy() - (n - 64), ocol)
