@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_dist(const int32_t* __restrict_
 // through the lanes one by one, so it is the sequential sum.
 __global__ __launch_bounds__(kBlock) void k_walk_weights(const int32_t* __restrict__ row_ptr, int32_t n,
                                                          double* __restrict__ C) {
-  const int32_t u = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t u = (int64_t)folded_block() * kWavesPerBlock + (threadIdx.x >> 6);
   if (u >= n) return;  // whole wave
   const int lane = threadIdx.x & (kWave - 1);
   const int32_t a = row_ptr[u], b = row_ptr[u + 1];
@@ -248,7 +248,7 @@ tsgne_status tsgne_build_P_walks(int32_t n, int64_t nnz, const int32_t* row_ptr_
       hipLaunchKernelGGL(k_walk_dist<true>, dim3(blocks_for(nnz)), dim3(kBlock), 0, s, row_of, col_d, nnz, X_d, d, C);
     else
       hipLaunchKernelGGL(k_walk_dist<false>, dim3(blocks_for(nnz)), dim3(kBlock), 0, s, row_of, col_d, nnz, X_d, d, C);
-    hipLaunchKernelGGL(k_walk_weights, dim3((unsigned)(((int64_t)n + kWavesPerBlock - 1) / kWavesPerBlock)),
+    hipLaunchKernelGGL(k_walk_weights, folded_grid(((int64_t)n + kWavesPerBlock - 1) / kWavesPerBlock, kBlock),
                        dim3(kBlock), 0, s, row_ptr_d, n, C);
   }
   hipLaunchKernelGGL(k_walks, dim3(blocks_for((int64_t)n * walks)), dim3(kBlock), 0, s, row_ptr_d, col_d, C, n, walks,

@@ -152,3 +152,16 @@ def test_neighbourhood_graph_of_2_26_nodes(gpu):
     orp, ocol = oracle.knn_graph(rp, col, 3)
     assert not krp[:n - 64].any()
     assert np.array_equal(krp[n - 64:].cpu().numpy(), orp) and np.array_equal(kcol.cpu().numpy() - (n - 64), ocol)
+
+
+def test_walks_of_2_26_nodes(gpu):
+    import torch
+    n = 2 ** 26 + 100                                       # a wave each
+    row_ptr, dcol, _, _ = late_graph(n, [(0, i) for i in range(1, 64)], gpu)
+    g = tsgne.tsgne_build_P_walks(row_ptr, dcol, torch.zeros((n, 1), dtype=torch.float32, device=gpu), 8, 2, 5)
+    # a leaf's 8 walks go through the hub to any of the 63 leaves alike, so 504 of them have at most
+    # 63 * 62 / 2 distinct ends and hardly fewer than 400; always to the same leaf they have 62
+    nnz = g.info()[1]
+    g.close()
+    torch.cuda.empty_cache()
+    assert 2 * 300 < nnz <= 63 * 62
