@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kBlock) void k_sqdist(const int32_t* __restrict__ r
                                                    const int32_t* __restrict__ mirror, int64_t nnz,
                                                    const float* __restrict__ X, int32_t d, double* __restrict__ D) {
   constexpr int64_t kGroups = kBlock / kDistLanes;
-  const int64_t e0 = (int64_t)blockIdx.x * kGroups * kDistPer + threadIdx.x / kDistLanes;
+  const int64_t e0 = (int64_t)folded_block() * kGroups * kDistPer + threadIdx.x / kDistLanes;
   const int sub = threadIdx.x & (kDistLanes - 1);
   int32_t other[kDistPer], row[kDistPer], far[kDistPer];
 #pragma unroll
@@ -463,8 +463,8 @@ hipError_t launch_mirror(const int32_t* row_ptr, const int32_t* col, int32_t n, 
 hipError_t launch_sqdist(const int32_t* row_of, const int32_t* col, const int32_t* mirror, int64_t nnz,
                          const float* X, int32_t d, double* D, hipStream_t s) {
   if (nnz == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sqdist, dim3(blocks_for((nnz + kDistPer - 1) / kDistPer * kDistLanes)), dim3(kBlock), 0, s,
-                     row_of, col, mirror, nnz, X, d, D);
+  hipLaunchKernelGGL(k_sqdist, folded_grid(blocks_for((nnz + kDistPer - 1) / kDistPer * kDistLanes), kBlock),
+                     dim3(kBlock), 0, s, row_of, col, mirror, nnz, X, d, D);
   return hipGetLastError();
 }
 

@@ -165,3 +165,29 @@ def test_walks_of_2_26_nodes(gpu):
     g.close()
     torch.cuda.empty_cache()
     assert 2 * 300 < nnz <= 63 * 62
+
+
+def lattice(n, reach, gpu):
+    """CSR on the device of a ring of n nodes, each joined to the `reach` before and after it."""
+    import torch
+    off = torch.cat([torch.arange(-reach, 0, device=gpu), torch.arange(1, reach + 1, device=gpu)])
+    col = torch.remainder(torch.arange(n, device=gpu)[:, None] + off, n).to(torch.int32)
+    for rows in (slice(0, reach), slice(n - reach, n)):
+        col[rows] = col[rows].sort(1).values
+    return (2 * reach * torch.arange(n + 1, device=gpu)).to(torch.int32), col.flatten()
+
+
+def test_distances_of_2_29_entries(gpu):
+    import torch
+    n, reach = 2 ** 24, 17                                  # eight lanes an entry
+    X = (torch.arange(n, device=gpu) % 2).to(torch.float32)[:, None].contiguous()
+    row_ptr, col = lattice(n, reach, gpu)
+    g = tsgne.tsgne_build_P(row_ptr, col, X, 20.0)
+    P = np.zeros(col.numel(), np.float32)
+    assert tsgne.lib().tsgne_graph_export(g.handle, None, None, None, P.ctypes.data, None) == tsgne.TSGNE_OK
+    g.close()
+    del row_ptr, col
+    torch.cuda.empty_cache()
+    small = [t.cpu().numpy() for t in lattice(64, reach, gpu)]
+    oP = oracle.build_P(small[0], small[1], X[:64].cpu().numpy(), 20.0)[0].reshape(64, 2 * reach)[reach] * 64 / n
+    assert np.abs(P.reshape(n, 2 * reach)[reach:n - reach] / oP.astype(np.float32) - 1).max() <= P_TOL
