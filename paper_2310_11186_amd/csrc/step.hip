@@ -831,8 +831,8 @@ __global__ __launch_bounds__(kBlock) void k_attract_light(const int32_t* __restr
   // Blocks are dealt to the XCDs in turn; renumber them so that each XCD
   // takes one contiguous range of rows, and its L2 sees the neighbours of
   // nearby rows (the grid is a multiple of kXcds).
-  const uint32_t per_xcd = gridDim.x / kXcds;
-  const uint32_t block = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+  const uint32_t per_xcd = gridDim.x * gridDim.y / kXcds, i0 = folded_block();
+  const uint32_t block = (i0 % kXcds) * per_xcd + i0 / kXcds;
   const int64_t t = (int64_t)block * kBlock + threadIdx.x;
   const int32_t i = (int32_t)min<int64_t>(t / kRowLanes, n - 1);
   const bool live = t / kRowLanes < n && (row_ptr[i + 1] - row_ptr[i]) <= kHeavyDegree;
@@ -1423,11 +1423,12 @@ hipError_t launch_zsum(const Workspace& ws, int precision, hipStream_t s, int32_
 hipError_t launch_attract(const tsgne_graph* g, const float2* Y, int precision, double2* out, hipStream_t s) {
   const bool split = precision != TSGNE_PREC_FP32;
   const unsigned lb = blocks_for((int64_t)g->n * kRowLanes, kBlock);
-  const unsigned lb8 = (lb + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
+  dim3 lb8 = folded_grid((lb + kXcds - 1) / kXcds, kBlock * kXcds);  // whole rounds over the XCDs
+  lb8.x *= kXcds;
   if (split)
-    hipLaunchKernelGGL(k_attract_light<true>, dim3(lb8), dim3(kBlock), 0, s, g->row_ptr, g->col, g->P, Y, g->n, out);
+    hipLaunchKernelGGL(k_attract_light<true>, lb8, dim3(kBlock), 0, s, g->row_ptr, g->col, g->P, Y, g->n, out);
   else
-    hipLaunchKernelGGL(k_attract_light<false>, dim3(lb8), dim3(kBlock), 0, s, g->row_ptr, g->col, g->P, Y, g->n, out);
+    hipLaunchKernelGGL(k_attract_light<false>, lb8, dim3(kBlock), 0, s, g->row_ptr, g->col, g->P, Y, g->n, out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || g->n_heavy == 0) return e;
   const unsigned hb = blocks_for(g->n_heavy, kWavesPerBlock);

@@ -191,3 +191,30 @@ def test_distances_of_2_29_entries(gpu):
     small = [t.cpu().numpy() for t in lattice(64, reach, gpu)]
     oP = oracle.build_P(small[0], small[1], X[:64].cpu().numpy(), 20.0)[0].reshape(64, 2 * reach)[reach] * 64 / n
     assert np.abs(P.reshape(n, 2 * reach)[reach:n - reach] / oP.astype(np.float32) - 1).max() <= P_TOL
+
+
+def test_attraction_of_2_29_nodes(gpu):
+    import torch
+    n = 2 ** 29 + 100                                       # eight lanes each
+    rp, col = tsgne.tsgne_csr_from_edges(64, [(i, j) for i in range(0, 60, 2) for j in range(i + 1, 64, 3)])
+    row_ptr = np.zeros(n + 1, np.int32)
+    row_ptr[n - 64:] = rp
+    P = np.full(col.shape[0], 1.0 / col.shape[0], np.float32)
+    g = tsgne.tsgne_graph_from_host_P(row_ptr, col + np.int32(n - 64), P)
+    Y = torch.zeros((n, 2), dtype=torch.float32, device=gpu)
+    y = np.random.default_rng(29).standard_normal((64, 2)).astype(np.float32)
+    Y[n - 64:] = torch.from_numpy(y).to(gpu)
+    A = torch.full((n, 2), -1.0, dtype=torch.float64, device=gpu)
+    tsgne.tsgne_attraction(g, Y, tsgne.TSGNE_PREC_SPLIT, A)
+    assert not A[:n - 64].any()
+    row, y64 = np.repeat(np.arange(64), np.diff(rp)), y.astype(np.float64)
+    d = y64[row] - y64[col]
+    pw = P / (1.0 + (d * d).sum(1))
+    exact, size = np.zeros((64, 2)), np.zeros((64, 2))
+    np.add.at(exact, row, pw[:, None] * d)
+    np.add.at(size, row, np.abs(pw[:, None] * d))
+    # FP32 terms of at most 8 roundings, FP64 sums
+    assert (np.abs(A[n - 64:].cpu().numpy() - exact) <= 8 * 2.0 ** -24 * np.maximum(size, np.abs(pw).max())).all()
+    g.close()
+    del Y, A
+    torch.cuda.empty_cache()
