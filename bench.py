@@ -15,7 +15,8 @@ kernel (the repulsion, timed with HIP events on its own stream; the layouts
 of the timed region run with phase timing on, so each step's launches are
 issued one by one between events; for layouts under 2 s, the time of a
 layout without phase timing, whose steps are two launches each, is reported
-beside it as layout_ms_replayed), the FP64 oracle timed on the host cores
+beside it as layout_ms_replayed, a name from when its steps were replayed from a
+capture), the FP64 oracle timed on the host cores
 over a bounded sample, and, for the default workload, a compact serving leg
 (48 requests of 1K-200K nodes, 500 iterations each: saturated and Poisson
 arrivals at 0.8x the saturated rate, continuous batching against one request

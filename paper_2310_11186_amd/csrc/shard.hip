@@ -155,7 +155,8 @@ std::vector<int2> shard_tiles(int32_t n, int32_t R, int32_t shard, int32_t n_sha
 // shard's tile count (its tiles over the chip's 1024 SIMDs rounded up, at
 // least the 64 / R a SIMD needs to hide latency, times the tile area, over
 // the tile's per-pair efficiency relative to R = 16, the values the
-// single-graph plan uses: measured on MI355X at 200K-500K nodes).
+// single-graph plan uses: measured on MI355X at 200K-500K nodes before the
+// reciprocals were grouped, see make_plan for what they are since).
 int32_t shard_tile_rows(int32_t n, int32_t n_shards) {
   const int32_t rs[6] = {16, 15, 14, 12, 8, 4};
   const double eff[6] = {1.0, 1.004, 0.996, 0.997, 0.969, 0.827};

@@ -278,7 +278,10 @@ __device__ __forceinline__ bool take_chunk(const int32_t* __restrict__ row_ptr, 
         if (acc[w]) atomicOr(&hacc[w], acc[w]);
       // The bits are exchanged by device atomics alone, so it is enough that
       // they have been performed before the count: a fence would write back
-      // the L2 as well, with every chunk.
+      // the L2 as well, with every chunk.  This relies on gfx950, not on the
+      // language's memory model: there vmcnt counts atomics without a result
+      // until the memory that device scope names has performed them (targets
+      // from gfx10 on count those apart).
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int32_t n_chunks = (row_ptr[v + 1] - row_ptr[v] + kChunk - 1) / kChunk;
       if (atomicAdd(&heavy_done[c.w], 1) == n_chunks - 1) {  // every other chunk has added its bits

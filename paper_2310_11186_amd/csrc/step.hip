@@ -3,7 +3,8 @@
 // of eq. (5) and the momentum/gains update, and KL(P || Q).
 //
 // Repulsion tiling.  Positions are cut into nb blocks of T = 64 * R.  A work
-// item is one tile (a, b) processed by one wave; each lane keeps R "resident"
+// item is one tile (a, b), processed by one wave (symmetric tiles of 2 and 4 rows
+// by as many waves, a diagonal one by a workgroup); each lane keeps R "resident"
 // rows of block a in registers.
 //  - Symmetric tiles (a < b): the 64-position sub-blocks of b travel around the
 //    wave (every lane reads the next column from LDS, and a column's force
@@ -1338,16 +1339,18 @@ RepulsionPlan make_plan(int32_t n, int32_t R, int32_t variant) {
   // spite of their lower per-pair efficiency.  Crossovers measured on MI355X
   // over whole layout steps: 1 row per lane up to about 3,500 nodes (a step of
   // 2,000 nodes takes 12.4 us with 1 row, 12.9 with 2, 16.3 with 4; of 3,500
-  // 12.2, 13.1 and 16.4), 2 rows up to about 11,000 (5,000 nodes: 16.8 us with
-  // 1 row, 15.3 with 2, 16.4 with 4; at 9,001 2 and 4 rows are within 4 %,
-  // 23.6 and 22.8, at 11,500 32.6 and 31.0), and from about 11,000 nodes on
-  // the cost model below.
+  // 12.2, 13.1 and 16.4), 2 rows up to 11,000, and from there on the cost model
+  // below.  2 rows are ahead of 4 at 5,000 nodes (15.3 us and 16.4; 1 row 16.8)
+  // and no longer at 9,001 (23.6 and 22.8) and 11,500 (32.6 and 31.0): since waves
+  // share their tiles the crossover lies between 5,000 and 9,001, and the bound,
+  // measured before, costs the sizes between up to 5 %.
   if (!tile_rows_supported(R) && p.variant == TSGNE_REPULSION_SYMMETRIC) {
     if (n <= kOneRowMaxNodes) R = 1;
     else if (n <= kTwoRowMaxNodes) R = 2;
   }
   if (!tile_rows_supported(R)) {
-    // Cost model: the tiles (one wave each) of the busiest SIMD, i.e. the
+    // Cost model: the tiles of the busiest SIMD (one wave each; those of 4 rows,
+    // now four waves each, are counted alike), i.e. the
     // tile count over the chip's 1024 SIMDs rounded up, times the tile area,
     // divided by the per-pair efficiency of that tile relative to R = 16
     // (tile-pair slots per second of the repulsion at 200K-500K nodes, where
