@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kBlock) void k_calibrate(const int32_t* __restrict_
                                                       const int32_t* __restrict__ heavy, int32_t n_heavy,
                                                       int32_t heavy_blocks, const double* __restrict__ D, double perp,
                                                       double* __restrict__ pcond, double* __restrict__ beta) {
-  const int64_t block = folded_block();
+  const int32_t block = (int32_t)folded_block();  // at most 2^31 / 16 + heavy_blocks
   if (block < heavy_blocks) {
     const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(block * (kBlock / kWave) + (threadIdx.x >> 6)));
     if (w >= n_heavy) return;
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kBlock) void k_calibrate(const int32_t* __restrict_
     calibrate_row<kWave>(D + b, deg, perp, pcond + b, beta + i, (int)(threadIdx.x & (kWave - 1)));
     return;
   }
-  const int64_t i = ((block - heavy_blocks) * kBlock + threadIdx.x) / kCalLanes;
+  const int64_t i = ((int64_t)(block - heavy_blocks) * kBlock + threadIdx.x) / kCalLanes;
   if (i >= n) return;  // whole groups
   const int64_t b = row_ptr[i], deg = (int64_t)row_ptr[i + 1] - b;
   if (deg > kHeavyDegree) return;
