@@ -437,7 +437,7 @@ __global__ __launch_bounds__(kBlock, W <= 4 ? 8 : 4) void k_sp_level(const int32
 //
 // Bound by writing X (d = 128, 300,000 nodes: 154 MB, 22 us at a fill's rate).
 // With 64 bytes a lane and all the planes that l0 could need this took 57 us,
-// now 30.
+// now 32.
 constexpr int kDecodeNodes = 64;
 
 template <int W, bool QUAD>
